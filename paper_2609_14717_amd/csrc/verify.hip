@@ -13,22 +13,65 @@
 //     a correction whose weights are all zero): y is the smallest token whose
 //     running integer sum exceeds floor(word * W / 2^32), W the total weight.
 //
-// One workgroup per sequence.  The first wavefront takes the acceptance
-// decisions with one ballot per 64 positions; then the workgroup streams the
-// selected row of p (and q) twice: once for the total weight, once for the
-// running sums, 1024 tokens per step with an exclusive scan across threads.
+// One workgroup of 16 wavefronts per sequence (no scratch memory reaches this
+// call, so a row's total cannot be summed across workgroups).  The first
+// wavefront takes the acceptance decisions with one ballot per 64 positions.
+// Then the row of p (and q) is read once: every wavefront sums the weights of
+// its own contiguous sixteenth, and only the sixteenth that holds the draw is
+// read again for the running sums.  The row is bound by what one CU can keep in
+// flight, so a lane has four 16-byte loads of each array outstanding (128 KiB
+// per workgroup).  Integer sums: any order gives the same result.
+// 32 sequences of 128000 tokens: 421 us with one load
+// in flight per thread, 256 threads and two passes, 20 us now.
 #include "co_kernels.h"
 
 namespace co {
 
 namespace {
 
-constexpr int kVerifyThreads = 256;
+constexpr int kVerifyThreads = 1024, kVerifyWaves = kVerifyThreads / 64;
+constexpr int kVerifyStep = 256;   // tokens of one wavefront load (four per lane)
+constexpr int kVerifyDepth = 4;    // such loads in flight per array
+constexpr int kFindPer = 8;        // tokens per thread and step of the draw's search
 
-__device__ __forceinline__ uint64_t fixed_weight(const float* p, const float* q, int64_t y) {
-  double d = static_cast<double>(p[y]);
-  if (q) d -= static_cast<double>(q[y]);
+// Rows start at any multiple of four bytes (vocabularies need not be multiples
+// of four, the arrays need not be 16-byte aligned); 16-byte global loads take
+// such addresses.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ uint64_t weight_of(double d) {
   return d > 0.0 ? static_cast<uint64_t>(d * 4294967296.0) : 0ull;
+}
+
+__device__ __forceinline__ double difference(float p, float q) {
+  return static_cast<double>(p) - static_cast<double>(q);
+}
+
+// The four weights of a load, w[k] of token k.  Below 1 (every probability but
+// a certainty) floor(2^32 d) fits 32 bits: one conversion instead of the
+// several of the 64-bit one.
+__device__ __forceinline__ void weights4(f32x4u p, f32x4u q, uint64_t (&w)[4]) {
+  double d[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) d[k] = difference(p[k], q[k]);
+  if (__any(d[0] >= 1.0 || d[1] >= 1.0 || d[2] >= 1.0 || d[3] >= 1.0)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = weight_of(d[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      w[k] = d[k] > 0.0 ? static_cast<uint32_t>(d[k] * 4294967296.0) : 0u;
+  }
+}
+
+// Tokens y .. y + 3 of a row, zeros from `end` on.
+__device__ __forceinline__ f32x4u load4(const float* r, int64_t y, int64_t end) {
+  if (y + 4 <= end) return *reinterpret_cast<const f32x4u*>(r + y);
+  f32x4u v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (y + k < end) v[k] = r[y + k];
+  return v;
 }
 
 __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int off) {
@@ -43,32 +86,80 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Sum of the weights of a row over the workgroup (every thread gets it).
-__device__ uint64_t row_total(const float* p, const float* q, int V, uint64_t* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint64_t s = 0;
-  for (int64_t y = tid; y < V; y += kVerifyThreads) s += fixed_weight(p, q, y);
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) s += shfl_xor_u64(s, m);
-  __syncthreads();   // red[] may still be read from a previous use
-  if (lane == 0) red[wave] = s;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+// Tokens per wavefront: whole loads, so that only the row's end is ragged.
+__device__ __forceinline__ int wave_tokens(int V) {
+  const int64_t unit = static_cast<int64_t>(kVerifyWaves) * kVerifyStep;
+  return static_cast<int>((V + unit - 1) / unit) * kVerifyStep;
 }
 
-// Smallest y with w(0) + ... + w(y) > t (t < the row's total weight).
-__device__ int row_find(const float* p, const float* q, int V, uint64_t t, uint64_t* red,
+// Sum of the weights of this wavefront's part of the row, into red[wave].
+template <bool HAS_Q>
+__device__ void part_total(const float* p, const float* q, int V, int R, uint64_t* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lo = static_cast<int>(min(static_cast<int64_t>(V), static_cast<int64_t>(wave) * R));
+  const int hi = static_cast<int>(min(static_cast<int64_t>(V), static_cast<int64_t>(lo) + R));
+  const f32x4u zero = {0.f, 0.f, 0.f, 0.f};
+  uint64_t s = 0;
+  int n = (hi - lo) / kVerifyStep;   // whole loads
+  const float* pp = p + lo + 4 * lane;
+  const float* qp = HAS_Q ? q + lo + 4 * lane : nullptr;
+  f32x4u pv[kVerifyDepth], qv[kVerifyDepth];
+  for (; n >= kVerifyDepth; n -= kVerifyDepth) {
+#pragma unroll
+    for (int u = 0; u < kVerifyDepth; ++u) {
+      pv[u] = *reinterpret_cast<const f32x4u*>(pp + u * kVerifyStep);
+      qv[u] = HAS_Q ? *reinterpret_cast<const f32x4u*>(qp + u * kVerifyStep) : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < kVerifyDepth; ++u) {
+      uint64_t w[4];
+      weights4(pv[u], qv[u], w);
+      s += (w[0] + w[1]) + (w[2] + w[3]);
+    }
+    pp += kVerifyDepth * kVerifyStep;
+    if (HAS_Q) qp += kVerifyDepth * kVerifyStep;
+  }
+  for (int64_t y = pp - p; y - 4 * lane < hi; y += kVerifyStep) {
+    uint64_t w[4];
+    weights4(load4(p, y, hi), HAS_Q ? load4(q, y, hi) : zero, w);
+    s += (w[0] + w[1]) + (w[2] + w[3]);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) s += shfl_xor_u64(s, m);
+  if (lane == 0) red[wave] = s;
+}
+
+__device__ uint64_t row_total(const float* p, const float* q, int V, int R, uint64_t* red) {
+  __syncthreads();   // red[] may still be read from a previous use
+  if (q) part_total<true>(p, q, V, R, red);
+  else part_total<false>(p, q, V, R, red);
+  __syncthreads();
+  uint64_t W = 0;
+  for (int v = 0; v < kVerifyWaves; ++v) W += red[v];
+  return W;
+}
+
+// Smallest y with w(0) + ... + w(y) > t (t < the row's total weight), from the
+// part totals in red[]: the part that holds it, then running sums over that part.
+__device__ int row_find(const float* p, const float* q, int V, int R, uint64_t t, uint64_t* red,
                         int* found) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) *found = -1;
   uint64_t base = 0;
-  for (int64_t c0 = 0; c0 < V; c0 += 4 * kVerifyThreads) {
-    const int64_t y0 = c0 + 4 * tid;
-    uint64_t w[4], own = 0;
+  int part = 0;
+  while (part < kVerifyWaves - 1 && base + red[part] <= t) base += red[part++];
+  const int64_t lo = static_cast<int64_t>(part) * R;
+  const int64_t hi = min(static_cast<int64_t>(V), lo + R);
+  if (tid == 0) *found = -1;
+  const f32x4u zero = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t c0 = lo; c0 < hi; c0 += kFindPer * kVerifyThreads) {
+    const int64_t y0 = c0 + kFindPer * tid;
+    uint64_t w[kFindPer / 4][4], own = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      w[k] = y0 + k < V ? fixed_weight(p, q, y0 + k) : 0ull;
-      own += w[k];
+    for (int j = 0; j < kFindPer / 4; ++j) {
+      const bool in = y0 + 4 * j < hi;
+      const int64_t y = in ? y0 + 4 * j : 0, end = in ? hi : 0;
+      weights4(load4(p, y, end), q ? load4(q, y, end) : zero, w[j]);
+      own += (w[j][0] + w[j][1]) + (w[j][2] + w[j][3]);
     }
     uint64_t inc = own;   // inclusive scan within the wavefront
 #pragma unroll
@@ -76,12 +167,12 @@ __device__ int row_find(const float* p, const float* q, int V, uint64_t t, uint6
       const uint64_t o = shfl_up_u64(inc, off);
       if (lane >= off) inc += o;
     }
-    __syncthreads();
+    __syncthreads();   // red[] and *found of the step before are read
     if (lane == 63) red[wave] = inc;
     __syncthreads();
     uint64_t before = base, total = 0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < kVerifyWaves; ++v) {
       if (v < wave) before += red[v];
       total += red[v];
     }
@@ -89,8 +180,8 @@ __device__ int row_find(const float* p, const float* q, int V, uint64_t t, uint6
     if (before <= t && t < before + own) {
       uint64_t c = before;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        c += w[k];
+      for (int k = 0; k < kFindPer; ++k) {
+        c += w[k / 4][k % 4];
         if (c > t) {
           *found = static_cast<int>(y0 + k);
           break;
@@ -107,7 +198,7 @@ __device__ int row_find(const float* p, const float* q, int V, uint64_t t, uint6
 __global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
   const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int B = a.B, V = a.V;
-  __shared__ uint64_t red[4];
+  __shared__ uint64_t red[kVerifyWaves];
   __shared__ int sh_m, sh_found;
   const int64_t prow0 = static_cast<int64_t>(s) * (B + 1);
   const int64_t qrow0 = static_cast<int64_t>(s) * B;
@@ -148,16 +239,17 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
   }
   const float* p = a.p + (prow0 + m) * V;
   const float* q = m < B ? a.q + (qrow0 + m) * V : nullptr;
-  uint64_t W = row_total(p, q, V, red);
+  const int R = wave_tokens(V);
+  uint64_t W = row_total(p, q, V, R, red);
   if (W == 0 && q) {
     q = nullptr;
-    W = row_total(p, q, V, red);
+    W = row_total(p, q, V, R, red);
   }
   int next = -1;
   if (W) {
     const uint64_t u = a.words[prow0 + B];
     const uint64_t t = u * (W >> 32) + ((u * (W & 0xFFFFFFFFull)) >> 32);   // floor(u W / 2^32)
-    next = row_find(p, q, V, t, red, &sh_found);
+    next = row_find(p, q, V, R, t, red, &sh_found);
   }
   if (tid == 0) {
     a.accept_len[s] = m;

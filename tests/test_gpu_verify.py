@@ -122,3 +122,20 @@ def test_verified_decisions_drive_the_round():
     np.testing.assert_array_equal(sc.rt["accept_len"].cpu().numpy(), want)
     np.testing.assert_array_equal((sc.st["ctx_len"] - ctx0).cpu().numpy(), want)
     np.testing.assert_array_equal(sc.st["carry_len"].cpu().numpy(), w.B - want)
+
+
+@pytest.mark.parametrize("V", [255, 256, 257, 4095, 4097, 16387, 65536, 131071, 160001])
+def test_verify_parts_of_a_row(V):
+    """Rows around the sixteenths a wavefront sums (whole 256-token loads), with
+    rows that start at every multiple of four bytes (V odd), a single search
+    step and two (above 131072 tokens), and a certainty (weight 2^32)."""
+    _gpu()
+    w = wl.RAGGED32.replace(B=3, seed=0x5EED25)
+    draft, p, q, words = wl.verify_inputs(w, 0, V, S=4)
+    x = (draft[0, 0] + V // 2) % V                        # rejected, all the residual on one token
+    p[0, 0, :] = 0.0
+    p[0, 0, x] = 1.0
+    q[0, 0, x] = 0.0
+    words[1, 3] = 0xFFFFFFFF                              # the draw's largest and smallest words
+    words[2, 3] = 0
+    _check(w, draft, p, q, words, f"parts V={V}")
