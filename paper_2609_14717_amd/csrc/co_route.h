@@ -1,8 +1,9 @@
 // One sequence's route step (Eq. 1; Algorithm 1 "Given" and steps 5-6;
-// greedy verification, Section 2 "Preliminaries"), for one wavefront: the
-// accepted prefix, the row descriptors and the new lengths.  Shared by the
-// route kernel and by the F product's launch, which can carry it as extra
-// workgroups (the F product itself does not read the descriptors then).
+// greedy verification, Section 2 "Preliminaries"): the accepted prefix, the row
+// descriptors and the new lengths.  One wavefront takes a sequence's window in
+// the route kernel and in the F product's launch, which can carry it as extra
+// workgroups (the F product itself does not read the descriptors then); a
+// whole workgroup takes a window of many rows.
 #pragma once
 
 #include "co_kernels.h"
@@ -48,45 +49,48 @@ __device__ __forceinline__ bool route_row_carried(const RouteArgs& a, int r) {
   return rejected;
 }
 
-__device__ __forceinline__ void route_sequence(const RouteArgs& a, int s, int lane) {
-  const int B = a.B;
-  const int p0 = a.ctx_len[s];
-  const int m = route_accepted(a, s, lane);
+// What a window cannot be routed for, before its pages are looked at.
+__device__ __forceinline__ int route_length_error(const RouteArgs& a, int p0) {
+  if (p0 < 0) return CO_ERR_LENGTH;
+  const int64_t cap = static_cast<int64_t>(a.max_pages) * kPage;
+  return static_cast<int64_t>(p0) + a.B > cap ? CO_ERR_CAPACITY : 0;
+}
 
+// Whether a page of the rows this thread takes (t, t + nt, ..) of the accepted
+// ones is out of range.
+__device__ __forceinline__ bool route_bad_page(const RouteArgs& a, int s, int p0, int m, int t,
+                                               int nt) {
+  const int32_t* pt = a.page_table + static_cast<int64_t>(s) * a.max_pages;
+  bool bad = false;
+  for (int j = t; j < m; j += nt) {
+    const int page = pt[(p0 + j) / kPage];
+    bad |= page < 0 || page >= a.num_pages;
+  }
+  return bad;
+}
+
+// Descriptors of rows t, t + nt, .. and (thread 0) the new lengths.
+__device__ __forceinline__ void route_write(const RouteArgs& a, int s, int p0, int m, int err,
+                                            int t, int nt) {
+  const int B = a.B;
   const bool carry_only = a.flags & CO_ROUTE_CARRY_ONLY;
   const bool baseline = a.flags & CO_BASELINE_MODE;
-  const int64_t cap = static_cast<int64_t>(a.max_pages) * kPage;
   const int32_t* pt = a.page_table + static_cast<int64_t>(s) * a.max_pages;
-
-  int err = 0;
-  if (p0 < 0) {
-    err = CO_ERR_LENGTH;
-  } else if (static_cast<int64_t>(p0) + B > cap) {
-    err = CO_ERR_CAPACITY;
-  } else if (!carry_only) {
-    bool bad = false;
-    for (int j = lane; j < m; j += 64) {
-      const int page = pt[(p0 + j) / kPage];
-      bad |= page < 0 || page >= a.num_pages;
-    }
-    if (__any(bad)) err = CO_ERR_PAGE_RANGE;
-  }
-
   int32_t* pos_out = a.row_pos + static_cast<int64_t>(s) * B;
   int32_t* dst_out = a.row_dst + static_cast<int64_t>(s) * B;
   if (err) {
-    for (int j = lane; j < B; j += 64) {
+    for (int j = t; j < B; j += nt) {
       pos_out[j] = p0 >= 0 ? p0 + j : 0;
       dst_out[j] = kSkip;
     }
-    if (lane == 0) {
+    if (t == 0) {
       a.accept_len[s] = 0;
       set_status(a.status, err);
     }
     return;
   }
 
-  for (int j = lane; j < B; j += 64) {
+  for (int j = t; j < B; j += nt) {
     const int pos = p0 + j;
     int32_t dst = kSkip;
     if (j < m) {
@@ -97,11 +101,21 @@ __device__ __forceinline__ void route_sequence(const RouteArgs& a, int s, int la
     pos_out[j] = pos;
     dst_out[j] = dst;
   }
-  if (lane == 0) {
+  if (t == 0) {
     a.accept_len[s] = m;
     a.ctx_len[s] = p0 + m;
     a.carry_len[s] = baseline ? 0 : B - m;
   }
+}
+
+__device__ __forceinline__ void route_sequence(const RouteArgs& a, int s, int lane) {
+  const int p0 = a.ctx_len[s];
+  const int m = route_accepted(a, s, lane);
+  int err = route_length_error(a, p0);
+  if (err == 0 && !(a.flags & CO_ROUTE_CARRY_ONLY) &&
+      __any(route_bad_page(a, s, p0, m, lane, 64)))
+    err = CO_ERR_PAGE_RANGE;
+  route_write(a, s, p0, m, err, lane, 64);
 }
 
 }  // namespace co
