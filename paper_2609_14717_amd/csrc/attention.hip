@@ -25,7 +25,7 @@
 //     record per slice and a small kernel combines them (log-sum-exp rule).
 //     Combining inside the persistent kernel would need a device-scope release
 //     per workgroup, which on this part writes back the L2 of the XCD.
-// fp32 path: per-chunk workgroups with plain VALU arithmetic through LDS.
+// fp32 path: per-chunk workgroups on the fp32 matrix instruction.
 #include <stdlib.h>
 #include <string.h>
 
@@ -149,24 +149,37 @@ __global__ __launch_bounds__(256) void attn_chunk_merge_kernel(AttnArgs a, int c
   }
 }
 
-// fp32 path: the same chunk partials, computed with plain VALU arithmetic through LDS,
-// always combined through the workspace records.
-template <int HD>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int chunk_pages, int n_chunks,
-                                                       int nq_pad) {
-  constexpr int KT = 32;
-  __shared__ float qs[64][HD + 1];
-  __shared__ float os[64][HD + 1];
-  __shared__ float ks[KT][HD + 1];
-  __shared__ float vs[KT][HD + 1];
-  __shared__ float sc[64][KT + 1];
-  __shared__ float m_run[64], l_run[64], alpha_s[64];
-  __shared__ int kvalid[KT];
+// fp32 path: one workgroup per chunk of pages, whose 32-key tiles (two pages)
+// its four wavefronts take in turn; the wavefronts' partials are merged in LDS,
+// and a segment of one chunk is finished there (longer ones leave records for
+// the merge kernel).  Products on v_mfma_f32_32x32x2_f32; key rows go through
+// LDS (whole 1 KiB loads, a tile ahead), value pages straight to registers:
+//   S^T = K . Q^T: lane l holds key row l % 32, dims 8c + 4 (l / 32) .. + 3;
+//   the scores then sit as query l % 32, keys 8 (r / 4) + 4 (l / 32) + r % 4 in
+//   register r, which is the B operand of O^T += V^T . P^T step by step, and V
+//   pages stored [head_dim][16 slots] give its A operand with 16-byte loads.
+// What bounds it is the latency of a chunk's few tiles behind its set-up.
+// 8 sequences of 100-4000 keys, 2 layers, 4 KV heads of 64: 35 us and 7 us for
+// the merge; with VALU dot products through LDS and a record per 64 keys, 133
+// and 19 us.
+template <int HD, int NQT>
+__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_f32_kernel(AttnArgs a,
+                                                                         int chunk_pages,
+                                                                         int n_chunks,
+                                                                         int nq_pad) {
+  constexpr int NQ = 32 * NQT, NW = 4, LD = HD + 4, MO = HD / 32, KC = HD / 8;
+  // the rotated queries [NQ][LD] and a key tile per wavefront [NW][32][HD]; then
+  // the wavefronts' partial outputs [NW][NQ][LD]
+  constexpr int KTILE = 32 * HD, CPR = HD / 4;   // floats; 16-byte chunks per key row
+  constexpr int STREAM = NQ * LD + NW * KTILE, MERGE = NW * NQ * LD;
+  __shared__ __align__(16) float smem[STREAM > MERGE ? STREAM : MERGE];
+  __shared__ float ml[2][NW][NQ];
 
   const int c = blockIdx.x, s = blockIdx.y;
   const int layer_local = blockIdx.z / a.Hkv, g = blockIdx.z % a.Hkv;
   const int layer = a.layer_begin + layer_local;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SeqInfo si = seq_info(a, s, chunk_pages);
   if (!si.ok) {
     if (c == 0 && tid == 0) set_status(a.status, CO_ERR_LENGTH);
@@ -189,52 +202,64 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int chunk_pag
   const float* Q = static_cast<const float*>(a.q);
   const float qscale = rsqrtf(static_cast<float>(HD)) * kLog2e;
 
-  for (int idx = tid; idx < nq * (HD / 2); idx += 256) {
-    const int n = idx / (HD / 2), p = idx % (HD / 2);
-    const float* qrow = Q + out_row(a, layer_local, s, g, n, G) * HD;
-    float lo = qrow[p], hi = qrow[p + HD / 2];
-    if (!(a.flags & CO_Q_PREROTATED)) {
-      float cs, sn;
-      rope_cos_sin(ctx + n / G, a.rope_inv[p], &cs, &sn);
-      const float l2 = lo * cs - hi * sn, h2 = hi * cs + lo * sn;
-      lo = l2;
-      hi = h2;
-    }
-    qs[n][p] = lo * qscale;
-    qs[n][p + HD / 2] = hi * qscale;
+  // one round trip: the chunk's page ids (lane i: page p_begin + i of a window
+  // of 64), this thread's query pairs and its rotation frequency (the pair
+  // index is the same in all of them)
+  int win = 0, idv = 0;
+  auto fetch_ids = [&](int w) {
+    win = w;
+    const int p = p_begin + 64 * w + lane;
+    idv = p < min(p_end, npc) ? a.page_table[static_cast<int64_t>(s) * a.max_pages + p] : 0;
+  };
+  fetch_ids(0);
+  constexpr int QI = NQ * (HD / 2) / 256;
+  static_assert(256 % (HD / 2) == 0, "one pair index per thread");
+  const int qp = tid % (HD / 2);
+  const double inv = a.rope_inv[qp];
+  float qlo[QI], qhi[QI];
+#pragma unroll
+  for (int i = 0; i < QI; ++i) {
+    const int n = (tid + 256 * i) / (HD / 2);
+    const float* qrow = Q + (n < nq ? out_row(a, layer_local, s, g, n, G) * HD : 0);
+    qlo[i] = qrow[qp];
+    qhi[i] = qrow[qp + HD / 2];
   }
-  for (int idx = tid; idx < 64 * HD; idx += 256) os[idx / HD][idx % HD] = 0.f;
-  if (tid < 64) {
-    m_run[tid] = -INFINITY;
-    l_run[tid] = 0.f;
-  }
-  __syncthreads();
 
+  f32x16 o[NQT][MO];
+  float m_run[NQT], l_run[NQT];   // l_run: this half-wavefront's keys
+#pragma unroll
+  for (int qt = 0; qt < NQT; ++qt) {
+#pragma unroll
+    for (int m = 0; m < MO; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[qt][m][r] = 0.f;
+    m_run[qt] = -INFINITY;
+    l_run[qt] = 0.f;
+  }
   const float* kc = static_cast<const float*>(a.k_cache);
   const float* vc = static_cast<const float*>(a.v_cache);
   const float* kk = static_cast<const float*>(a.k_carry);
   const float* vk = static_cast<const float*>(a.v_carry);
-  for (int lp0 = p_begin; lp0 < p_end; lp0 += 2) {
-    // stage 32 keys (two logical pages): resolve both pages first, then issue
-    // every element load of the tile before any is used
-    const float* kp[2];
-    const float* vp[2];
-    int nvalid[2];
+  const float *kp[2], *vp[2];
+  int nv[2];
+  // the two pages of the tile at lp0: addresses and valid keys
+  auto resolve = [&](int lp0) {
+    if ((lp0 - p_begin) / 64 != win) fetch_ids((lp0 - p_begin) / 64);   // a pair never straddles
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const int lp = lp0 + q;
-      kp[q] = vp[q] = nullptr;
-      nvalid[q] = 0;
+      const int lp = lp0 + q, id = __builtin_amdgcn_readlane(idv, (lp - p_begin) & 63);
+      kp[q] = kk;   // nothing to read: carry page 0, its keys masked
+      vp[q] = vk;
+      nv[q] = 0;
       if (lp >= p_end) continue;
       if (lp < npc) {
-        const int phys = a.page_table[static_cast<int64_t>(s) * a.max_pages + lp];
-        if (phys >= 0 && phys < a.num_pages) {
+        if (id >= 0 && id < a.num_pages) {
           const int64_t off =
-              ((static_cast<int64_t>(layer) * a.num_pages + phys) * a.Hkv + g) * kPage * HD;
+              ((static_cast<int64_t>(layer) * a.num_pages + id) * a.Hkv + g) * kPage * HD;
           kp[q] = kc + off;
           vp[q] = vc + off;
-          nvalid[q] = min(kPage, ctx - lp * kPage);
-        } else if (tid == 0) {
+          nv[q] = min(kPage, ctx - lp * kPage);
+        } else if (lane == 0) {
           set_status(a.status, CO_ERR_PAGE_RANGE);
         }
       } else {
@@ -243,76 +268,167 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int chunk_pag
             (((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp) * a.Hkv + g) * kPage * HD;
         kp[q] = kk + off;
         vp[q] = vk + off;
-        nvalid[q] = min(kPage, carry - cp * kPage);
+        nv[q] = min(kPage, carry - cp * kPage);
       }
     }
-    constexpr int PER = KT * HD / 256;   // elements of the tile staged per thread
-    float kr[PER], vr[PER];
+  };
+  // the tile's key rows into this wavefront's slot: 1 KiB per load, a row's
+  // chunks XOR-permuted by the row, so that sixteen lanes reading one logical
+  // chunk of sixteen rows hit sixteen different bank groups
+  float* kslot = smem + NQ * LD + wave * KTILE;
+  auto issue_k = [&]() {
+    constexpr int RPL = 64 / CPR;   // rows per load
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = tid + e * 256, key = idx / HD, dd = idx % HD;
-      const int q = key >> 4, slot = key & 15;
-      const bool ok = slot < nvalid[q];
-      kr[e] = ok ? kp[q][slot * HD + dd] : 0.f;
-      vr[e] = ok ? vp[q][dd * kPage + slot] : 0.f;
+    for (int j = 0; j < 32 / RPL; ++j) {
+      const int r = (j * RPL) % kPage + lane / CPR, ch = (lane % CPR) ^ (r & 15);
+      lds_dma16(kp[j * RPL / kPage] + r * HD + ch * 4, kslot + j * 256);
+    }
+  };
+  int lp0 = p_begin + 2 * wave;
+  if (lp0 < p_end) {
+    resolve(lp0);
+    issue_k();
+  }
+#pragma unroll
+  for (int i = 0; i < QI; ++i) {
+    const int n = (tid + 256 * i) / (HD / 2);
+    float lo = n < nq ? qlo[i] : 0.f, hi = n < nq ? qhi[i] : 0.f;
+    if (!(a.flags & CO_Q_PREROTATED)) {
+      float cs, sn;
+      rope_cos_sin(ctx + n / G, inv, &cs, &sn);
+      const float l2 = lo * cs - hi * sn, h2 = hi * cs + lo * sn;
+      lo = l2;
+      hi = h2;
+    }
+    smem[n * LD + qp] = lo * qscale;
+    smem[n * LD + qp + HD / 2] = hi * qscale;
+  }
+  __syncthreads();   // every wavefront: its first keys are waited for below
+  for (; lp0 < p_end; lp0 += 2 * NW) {
+    f32x4 vf[MO][4];
+    const bool partial = nv[0] < kPage || nv[1] < kPage;
+    auto load_v = [&]() {
+#pragma unroll
+      for (int m = 0; m < MO; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          vf[m][j] = *reinterpret_cast<const f32x4*>(vp[j >> 1] + (32 * m + r32) * kPage + 8 * (j & 1) + 4 * h);
+    };
+    wait_vmcnt<0>();   // the key rows are in
+    asm volatile("" ::: "memory");
+    load_v();   // in flight over the first product
+    f32x16 sc[NQT];
+#pragma unroll
+    for (int qt = 0; qt < NQT; ++qt) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[qt][r] = 0.f;
+#pragma unroll
+      for (int x = 0; x < KC; ++x) {
+        const f32x4 q4 = *reinterpret_cast<const f32x4*>(smem + (qt * 32 + r32) * LD + 8 * x + 4 * h);
+        const f32x4 k4 = *reinterpret_cast<const f32x4*>(kslot + r32 * HD + (((2 * x + h) ^ (r32 & 15)) << 2));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[qt] = mfma32x32x2_f32(k4[e], q4[e], sc[qt]);
+      }
+    }
+    const int nv0 = nv[0], nv1 = nv[1];
+    if (lp0 + 2 * NW < p_end) {   // the next tile's keys, once this tile's are read
+#pragma unroll
+      for (int qt = 0; qt < NQT; ++qt) asm volatile("" : "+v"(sc[qt]));
+      resolve(lp0 + 2 * NW);
+      issue_k();
     }
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = tid + e * 256, key = idx / HD, dd = idx % HD;
-      ks[key][dd] = kr[e];
-      vs[key][dd] = vr[e];
-      if (dd == 0) kvalid[key] = (key & 15) < nvalid[key >> 4];
-    }
-    __syncthreads();
-    for (int idx = tid; idx < nq * KT; idx += 256) {
-      const int n = idx / KT, key = idx % KT;
-      float dot = 0.f;
-      for (int dd = 0; dd < HD; ++dd) dot += qs[n][dd] * ks[key][dd];
-      sc[n][key] = kvalid[key] ? dot : -INFINITY;
-    }
-    __syncthreads();
-    if (tid < nq) {
-      float mx = -INFINITY;
-      for (int key = 0; key < KT; ++key) mx = fmaxf(mx, sc[tid][key]);
-      const float m_new = fmaxf(m_run[tid], mx);
-      const float al = (m_new == -INFINITY) ? 1.f : exp2f(m_run[tid] - m_new);
+    for (int qt = 0; qt < NQT; ++qt) {
+      if (partial) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (8 * ((r >> 2) & 1) + 4 * h + (r & 3) >= ((r >> 3) ? nv1 : nv0)) sc[qt][r] = -INFINITY;
+      }
+      float mx = sc[qt][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[qt][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m_run[qt], mx);
+      const float al = (m_new == -INFINITY) ? 1.f : exp2f(m_run[qt] - m_new);
       const float base = (m_new == -INFINITY) ? 0.f : m_new;
       float sum = 0.f;
-      for (int key = 0; key < KT; ++key) {
-        const float p = exp2f(sc[tid][key] - base);
-        sc[tid][key] = p;
-        sum += p;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sc[qt][r] = exp2f(sc[qt][r] - base);
+        sum += sc[qt][r];
       }
-      l_run[tid] = l_run[tid] * al + sum;
-      m_run[tid] = m_new;
-      alpha_s[tid] = al;
+      l_run[qt] = l_run[qt] * al + sum;
+      m_run[qt] = m_new;
+#pragma unroll
+      for (int m = 0; m < MO; ++m) o[qt][m] *= al;
     }
-    __syncthreads();
-    for (int idx = tid; idx < nq * HD; idx += 256) {
-      const int n = idx / HD, dd = idx % HD;
-      float v = os[n][dd] * alpha_s[n];
-      for (int key = 0; key < KT; ++key) v += sc[n][key] * vs[key][dd];
-      os[n][dd] = v;
+    if (partial) {   // slots past the length may hold anything
+#pragma unroll
+      for (int m = 0; m < MO; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (8 * (j & 1) + 4 * h + e >= ((j >> 1) ? nv1 : nv0)) vf[m][j][e] = 0.f;
     }
-    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MO; ++m)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int qt = 0; qt < NQT; ++qt)
+            o[qt][m] = mfma32x32x2_f32(vf[m][j][e], sc[qt][4 * j + e], o[qt][m]);
   }
-  if (si.nch == 1) {
-    float* out = static_cast<float*>(a.out);
-    for (int idx = tid; idx < nq * HD; idx += 256) {
-      const int n = idx / HD;
-      const float inv = l_run[n] > 0.f ? 1.f / l_run[n] : 0.f;
-      out[out_row(a, layer_local, s, g, n, G) * HD + idx % HD] = os[n][idx % HD] * inv;
+  __syncthreads();   // the queries are read: their place takes the partials
+#pragma unroll
+  for (int qt = 0; qt < NQT; ++qt) {
+    const int n = qt * 32 + r32;
+#pragma unroll
+    for (int m = 0; m < MO; ++m)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = o[qt][m][4 * r4 + e];
+        *reinterpret_cast<f32x4*>(smem + (wave * NQ + n) * LD + 32 * m + 8 * r4 + 4 * h) = v;
+      }
+    const float l_tot = l_run[qt] + __shfl_xor(l_run[qt], 32);
+    if (h == 0) {
+      ml[0][wave][n] = m_run[qt];
+      ml[1][wave][n] = l_tot;
     }
-    if (a.lse && tid < nq)
-      a.lse[out_row(a, layer_local, s, g, tid, G)] =
-          l_run[tid] > 0.f ? (m_run[tid] + log2f(l_run[tid])) * kLn2 : -INFINITY;
-    return;
   }
-  float* part = record_ptr(a, layer_local, s, g, c, n_chunks, nq_pad);
-  for (int idx = tid; idx < nq * HD; idx += 256) part[idx] = os[idx / HD][idx % HD];
-  if (tid < nq) {
-    part[nq_pad * HD + tid] = m_run[tid];
-    part[nq_pad * HD + nq_pad + tid] = l_run[tid];
+  __syncthreads();
+  // one thread per (query row, four dims): log-sum-exp rule over the wavefronts
+  float* part = si.nch > 1 ? record_ptr(a, layer_local, s, g, c, n_chunks, nq_pad) : nullptr;
+  float* out = static_cast<float*>(a.out);
+  for (int idx = tid; idx < nq * (HD / 4); idx += 256) {
+    const int n = idx / (HD / 4), d = (idx % (HD / 4)) * 4;
+    float M = ml[0][0][n];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
+    float den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float mw = ml[0][w][n];
+      const float wgt = (mw == -INFINITY) ? 0.f : exp2f(mw - M);
+      den += wgt * ml[1][w][n];
+      acc += wgt * *reinterpret_cast<const f32x4*>(smem + (w * NQ + n) * LD + d);
+    }
+    if (part) {
+      *reinterpret_cast<f32x4*>(part + n * HD + d) = acc;
+      if (d == 0) {
+        part[nq_pad * HD + n] = M;
+        part[nq_pad * HD + nq_pad + n] = den;
+      }
+    } else {
+      const int64_t row = out_row(a, layer_local, s, g, n, G);
+      *reinterpret_cast<f32x4*>(out + row * HD + d) = acc * (den > 0.f ? 1.f / den : 0.f);
+      if (a.lse && d == 0) a.lse[row] = den > 0.f ? (M + log2f(den)) * kLn2 : -INFINITY;
+    }
   }
 }
 
@@ -2327,9 +2443,11 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
       }
     }
   } else {
-    // fp32 path: chunks of pages, one workgroup each; short chunks, so that a
-    // short context still spreads over many workgroups
-    p.chunk_pages = 4;
+    // fp32 path: chunks of pages, one workgroup each, two tiles per wavefront:
+    // short contexts end in one chunk (no records, no merge launch), longer ones
+    // leave a record per 256 keys (a quarter of the records of 64-key chunks,
+    // whose merge took 19 us instead of 7 in the batch above attn_f32_kernel)
+    p.chunk_pages = 16;
     while ((max_lp + p.chunk_pages - 1) / p.chunk_pages > kMaxMergeChunks) p.chunk_pages *= 2;
     p.ok = p.chunk_pages <= kMaxChunkPages;
     p.n_chunks = (max_lp + p.chunk_pages - 1) / p.chunk_pages;
@@ -2455,10 +2573,17 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
     return hipGetLastError();
   }
   const dim3 grid(p.n_chunks, a.S, layer_count * a.Hkv);
-  if (a.hd == 64)
-    hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, stream, a, p.chunk_pages, p.n_chunks, p.nq_pad);
-  else
-    hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, stream, a, p.chunk_pages, p.n_chunks, p.nq_pad);
+#define CO_F32_LAUNCH(HD, NQT)                                                                   \
+  hipLaunchKernelGGL((attn_f32_kernel<HD, NQT>), grid, dim3(256), 0, stream, a, p.chunk_pages,   \
+                     p.n_chunks, p.nq_pad)
+  if (a.hd == 64) {
+    if (one) CO_F32_LAUNCH(64, 1);
+    else CO_F32_LAUNCH(64, 2);
+  } else {
+    if (one) CO_F32_LAUNCH(128, 1);
+    else CO_F32_LAUNCH(128, 2);
+  }
+#undef CO_F32_LAUNCH
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || p.n_chunks <= 1) return err;
   hipLaunchKernelGGL(attn_chunk_merge_kernel<float>, fgrid, dim3(256), 0, stream, a, p.chunk_pages,

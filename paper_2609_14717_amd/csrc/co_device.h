@@ -120,6 +120,12 @@ __device__ __forceinline__ f32x4 mfma16x16x32(u16x8 a, u16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
 
+// v_mfma_f32_32x32x2_f32: acc[32x32] += A[32x2] * B[2x32], fp32 throughout.
+// Lane l holds A row (l % 32) and B column (l % 32) at k = l / 32; acc as above.
+__device__ __forceinline__ f32x16 mfma32x32x2_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 // Rotary angle of pair index i at position pos: pos * theta^(-2i/hd).  The product
 // and the reduction to [-pi, pi] are done in fp64 so that positions of 10^5 keep
 // fp32 accuracy after the reduction; sin/cos are then taken in fp32.

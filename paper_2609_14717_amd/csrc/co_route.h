@@ -49,6 +49,30 @@ __device__ __forceinline__ bool route_row_carried(const RouteArgs& a, int r) {
   return rejected;
 }
 
+// The same for the rows of a tile of BM rows from m0, whose products do not wait
+// for it: every lane of each wavefront loads the tokens of one of the 64 rows
+// that end with the tile, and one ballot at the end tells where a row's
+// sequence was first rejected.  Reaches back to the start of every sequence in
+// the tile when B - 1 <= 64 - BM (ok()); longer windows take route_row_carried.
+template <int BM>
+struct RouteTile {
+  int32_t d, t;
+  __device__ static bool ok(const RouteArgs& a) { return a.B - 1 <= 64 - BM; }
+  __device__ static int base(int m0) { return m0 + BM - 64; }
+  __device__ void load(const RouteArgs& a, int m0, int M, int lane) {
+    const int r = min(max(base(m0) + lane, 0), M - 1);
+    d = a.draft[r];
+    t = (a.flags & CO_ROUTE_ACCEPT_BITS) ? 0 : a.target[r];
+  }
+  // row r of the tile (r < M); called by whole wavefronts
+  __device__ bool carried(const RouteArgs& a, int m0, int r) const {
+    const bool rej = (a.flags & CO_ROUTE_ACCEPT_BITS) ? d == 0 : d != t;
+    const uint64_t mask = __ballot(rej);
+    const int b = base(m0), lo = r / a.B * a.B - b, hi = r - b;   // 0 <= lo <= hi < 64
+    return ((mask >> lo) & (~0ull >> (63 - (hi - lo)))) != 0;
+  }
+};
+
 // What a window cannot be routed for, before its pages are looked at.
 __device__ __forceinline__ int route_length_error(const RouteArgs& a, int p0) {
   if (p0 < 0) return CO_ERR_LENGTH;

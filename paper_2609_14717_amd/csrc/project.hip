@@ -18,7 +18,8 @@
 // hold E accumulates F(E), added to carried rows in the epilogue.  Skinny
 // shapes (few rows, long K) split K across workgroups deterministically
 // through an fp32 workspace.
-// fp32: a plain LDS-tiled VALU GEMM feeding the same epilogues.
+// fp32: the same two products on v_mfma_f32_32x32x2_f32, K split over the
+// sixteen wavefronts of a workgroup.
 #include <stdlib.h>
 
 #include <type_traits>
@@ -114,11 +115,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
   const bool carry_add = HAS_E || g.fe != nullptr;
   const bool need_rows = carry_add || g.mode == kModeKV || g.z_rows != 0;
   int rd_dst = 0, rd_pos = 0;
+  // where the route runs beside this product, carried rows are decided from the
+  // tokens: loaded here, compared after the main loop where one ballot reaches
+  constexpr int RBM = BM < 64 ? BM : 64;
+  RouteTile<RBM> tok{0, 0};
+  const bool beside = g.route_blocks > 0 && !(g.route.flags & (CO_ROUTE_ACCEPT_ALL | CO_BASELINE_MODE));
+  const bool by_ballot = BM < 64 && beside && RouteTile<RBM>::ok(g.route);
   if (need_rows) {
     const int r = min(m0 + (tid % BM), g.M - 1);
-    if (g.route_blocks > 0)   // the route runs beside this product: decide from the tokens
+    if (by_ballot)
+      tok.load(g.route, m0, g.M, lane);
+    else if (beside)
       rd_dst = route_row_carried(g.route, r) ? -1 : 0;
-    else
+    else if (g.route_blocks == 0)
       rd_dst = g.row_dst[r];
     if (g.mode == kModeKV) rd_pos = g.kv.row_pos[r];
   }
@@ -281,7 +290,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
   if (g.mode == kModeKV && tid < g.kv.hd / 2) inv_tab[tid] = rope_table<uint16_t>(g.kv, tid);
   __shared__ float fe_lds[BN];
   __shared__ int dst_lds[BM], pos_lds[BM];
-  asm volatile("" : "+v"(rd_dst), "+v"(rd_pos));
+  asm volatile("" : "+v"(rd_dst), "+v"(rd_pos), "+v"(tok.d), "+v"(tok.t));
+  if (need_rows && by_ballot)
+    rd_dst = tok.carried(g.route, m0, min(m0 + (tid % BM), g.M - 1)) ? -1 : 0;
   if (need_rows && tid < BM) {
     dst_lds[tid] = rd_dst;
     pos_lds[tid] = rd_pos;
@@ -632,56 +643,172 @@ __global__ __launch_bounds__(128 * WGN, 1) void gemm_wide_kernel(GemmArgs g, int
 }
 
 // ------------------------------------------------------------- fp32 GEMM
+//
+// One 32 x 32 tile per workgroup of sixteen wavefronts, each of which takes a
+// sixteenth of K for the whole tile; the sixteen partial tiles are summed in
+// LDS in wavefront order, so no product needs a K split over workgroups, fp32
+// partials in memory or a launch that sums them.  The shapes this path serves
+// (tens to hundreds of rows) are bound by the latency of the operand loads:
+// every wavefront keeps two stages of 16 k in flight in a ring of its own,
+// filled by direct-to-LDS loads that cover 64 bytes of a row with four lanes
+// (16-byte loads straight into the operand registers touch 32 rows per
+// instruction and took 31 us instead of 23 for the first product below), with no
+// barrier in the loop.
+// A step of 8 k: lane l reads A row and B row (l % 32), k = 4 (l / 32) .. + 3
+// as 16 bytes each; MFMA e multiplies element e of both, so the two halves of
+// the wavefront supply k = e and k = 4 + e.
+//   F:   Z[row][n0 + col], rows x = h + E where carried
+//   K/V: column c < 16 of tile j is pair dim p = 16 j + c of its head segment,
+//        column 16 + c its partner p + hd/2, so that every tile holds whole
+//        rotation pairs whatever the head width; stored rotated and scattered
+//   partial (K/V with the key norm, which needs whole heads): fp32 [M][N]
+// 128 x 1024 x 2560, then 128 x 1024 x 1024 and the stores: 23 + 11 us; the VALU
+// kernel with 32 and 16 K splits and its two summing launches took 63 us.
+constexpr int kF32Waves = 16, kF32Tile = 32;
+constexpr int kF32E = 4096;   // E values staged in LDS; longer K reads them where they are used
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  constexpr int BM = 32, BN = 64, BK = 32;
-  __shared__ float sa[BM][BK + 1];
-  __shared__ float sb[BN][BK + 1];
-  const int tid = threadIdx.x;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int tr = tid / 16, tc = tid % 16;
-  const float* A = static_cast<const float*>(g.A);
-  const float* Bw = static_cast<const float*>(g.B);
-  const float* E = static_cast<const float*>(g.e);
-  // K split blockIdx.z: k in [kb, ke), its partial product in slice blockIdx.z
-  const int kb = blockIdx.z * g.k_per_split;
-  const int ke = min(g.K, kb + g.k_per_split);
-  float* out = g.partial + static_cast<int64_t>(blockIdx.z) * g.M * g.N;
-  float acc[2][4] = {};
-  for (int k0 = kb; k0 < ke; k0 += BK) {
-    for (int c = tid; c < BM * BK; c += 256) {
-      const int r = c / BK, k = c % BK, gr = m0 + r;
-      float v = 0.f;
-      if (gr < g.M) {
-        v = A[static_cast<int64_t>(gr) * g.K + k0 + k];
-        if (E && is_carry_row(g.row_dst[gr])) v += E[k0 + k];
-      }
-      sa[r][k] = v;
+__global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(GemmArgs g) {
+  constexpr int BT = kF32Tile, BK = 16, NS = 2;   // tile edge; k per stage; stages in the ring
+  constexpr int ROWB = BK * 4, OPB = BT * ROWB, STAGE = 2 * OPB, NL = STAGE / 1024;
+  static_assert(BT * BT * 4 <= NS * STAGE, "a partial tile fits in its wavefront's ring");
+  __shared__ __align__(16) unsigned char ring[kF32Waves * NS * STAGE];
+  __shared__ __align__(16) float e_lds[kF32E];
+  __shared__ float tile[BT][BT + 1];
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row_tiles = (g.M + BT - 1) / BT;
+  if (static_cast<int>(blockIdx.y) >= row_tiles) {   // the route step: one wavefront per sequence
+    if (blockIdx.x == 0) {
+      const int s = (blockIdx.y - row_tiles) * kF32Waves + wave;
+      if (s < g.route.S) route_sequence(g.route, s, lane);
     }
-    for (int c = tid; c < BN * BK; c += 256) {
-      const int r = c / BK, k = c % BK, gn = n0 + r;
-      sb[r][k] = gn < g.N ? Bw[static_cast<int64_t>(gn) * g.K + k0 + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < BK; ++k) {
-      const float a0 = sa[tr][k], a1 = sa[tr + 16][k];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float b = sb[tc + 16 * j][k];
-        acc[0][j] += a0 * b;
-        acc[1][j] += a1 * b;
-      }
-    }
-    __syncthreads();
+    return;
   }
+  const int m0 = blockIdx.y * BT, nt = blockIdx.x;
+  const bool kv = g.mode == kModeKV;
+  const int half = g.kv.hd / 2, tps = kv ? half / 16 : 1;   // tiles per head segment
+  const int seg = nt / tps, p0 = nt % tps * 16;             // K/V: segment and first pair dim
+  // this wavefront's stages of 16 k: [u0, u1) of K / 16 (K is a multiple of 64)
+  const int U = g.K / BK, u0 = U * wave / kF32Waves, u1 = U * (wave + 1) / kF32Waves;
+  // load j of a stage fills 16 rows of A (j < 2) or B; a row's four 16-byte
+  // chunks are XOR-permuted by (row / 4) so that sixteen lanes reading one
+  // logical chunk of sixteen rows hit sixteen different bank groups
+  const float* src[NL];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + tr + 16 * i, col = n0 + tc + 16 * j;
-      if (row < g.M && col < g.N) out[static_cast<int64_t>(row) * g.N + col] = acc[i][j];
+  for (int j = 0; j < NL; ++j) {
+    const int r = (j & 1) * 16 + (lane >> 2), chunk = (lane & 3) ^ ((r >> 2) & 3);
+    const float* base;
+    if (j < NL / 2) {
+      base = static_cast<const float*>(g.A) + static_cast<int64_t>(min(m0 + r, g.M - 1)) * g.K;
+    } else {
+      const int n = kv ? seg * g.kv.hd + p0 + (r & 15) + (r >> 4) * half : nt * BT + r;
+      base = static_cast<const float*>(g.B) + static_cast<int64_t>(min(n, g.N - 1)) * g.K;
     }
+    src[j] = base + chunk * 4;
+  }
+  unsigned char* mine = ring + wave * NS * STAGE;
+  const uint32_t ring_lds = lds_addr(mine);
+  auto issue = [&](int u) {
+    const uint32_t st = ring_lds + ((u - u0) % NS) * STAGE;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) lds_dma16_opaque(src[j] + u * BK, st + j * 1024);
+  };
+  // K/V: the row and pair this thread stores at the end
+  int st_dst = 0, st_pos = 0;
+  const int st_row = m0 + (tid >> 4), st_p = p0 + (tid & 15);
+  if (kv) {
+    const int r = min(st_row, g.M - 1);
+    st_dst = g.row_dst[r];
+    st_pos = g.kv.row_pos[r];
+  }
+  // one round trip for the first stages, E and what decides the carried rows
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+    if (u0 + i < u1) issue(u0 + i);
+  const float* E = static_cast<const float*>(g.e);
+  const bool beside = g.route_blocks > 0;
+  if (beside && (g.route.flags & (CO_ROUTE_ACCEPT_ALL | CO_BASELINE_MODE))) E = nullptr;
+  const bool e_staged = g.K <= kF32E;
+  bool add_e = false;
+  if (E) {   // uniform
+    const int arow = min(m0 + r32, g.M - 1);
+    RouteTile<BT> tok{0, 0};
+    const bool by_ballot = beside && RouteTile<BT>::ok(g.route);
+    int dst = 0;
+    if (by_ballot) tok.load(g.route, m0, g.M, lane);
+    else if (!beside) dst = g.row_dst[arow];
+    if (e_staged)
+      for (int k = tid * 4; k < g.K; k += 256 * kF32Waves)
+        *reinterpret_cast<f32x4*>(e_lds + k) = *reinterpret_cast<const f32x4*>(E + k);
+    if (by_ballot) add_e = tok.carried(g.route, m0, arow);
+    else add_e = beside ? route_row_carried(g.route, arow) : is_carry_row(dst);
+    if (e_staged) __syncthreads();
+  }
+  const int swz = (r32 >> 2) & 3;
+
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int u = u0; u < u1; ++u) {
+    if (u + 1 < u1) wait_vmcnt<NL>();
+    else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    const unsigned char* st = mine + ((u - u0) % NS) * STAGE;
+    f32x4 x[BK / 8], b[BK / 8];
+#pragma unroll
+    for (int i = 0; i < BK / 8; ++i) {
+      const int off = r32 * ROWB + (((2 * i + h) ^ swz) << 4);
+      x[i] = *reinterpret_cast<const f32x4*>(st + off);
+      b[i] = *reinterpret_cast<const f32x4*>(st + OPB + off);
+    }
+    if (E) {
+#pragma unroll
+      for (int i = 0; i < BK / 8; ++i) {
+        const int k = u * BK + 8 * i + 4 * h;
+        f32x4 ev;
+        if (e_staged) ev = *reinterpret_cast<const f32x4*>(e_lds + k);
+        else ev = *reinterpret_cast<const f32x4*>(E + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[i][e] = add_e ? x[i][e] + ev[e] : x[i][e];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < BK / 8; ++i) asm volatile("" : "+v"(x[i]), "+v"(b[i]));   // read before the slot refills
+    if (u + NS < u1) issue(u + NS);
+#pragma unroll
+    for (int i = 0; i < BK / 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = mfma32x32x2_f32(x[i][e], b[i][e], acc);
+  }
+  // the partial tile into this wavefront's own (drained) part of the ring
+  constexpr int PLD = NS * STAGE / 4;   // floats from one wavefront's part to the next
+  float* sc = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    sc[wave * PLD + (8 * (r >> 2) + 4 * h + (r & 3)) * BT + r32] = acc[r];
+  __syncthreads();
+  // thread t sums element t of the tile over the wavefronts, in order
+  float v = sc[tid];
+#pragma unroll
+  for (int w = 1; w < kF32Waves; ++w) v += sc[w * PLD + tid];
+  const int row = tid >> 5, col = tid & 31;
+  if (!kv) {
+    const int gr = m0 + row, gc = nt * BT + col;
+    if (gr >= g.M || gc >= g.N) return;
+    const int64_t o = static_cast<int64_t>(gr) * g.N + gc;
+    if (g.mode == kModePartial) g.partial[o] = v;
+    else if (g.z_rows == 0 || z_row_selected(g.z_rows, g.row_dst[gr])) static_cast<float*>(g.z_out)[o] = v;
+    return;
+  }
+  tile[row][col] = v;
+  asm volatile("" : "+v"(st_dst), "+v"(st_pos));   // loaded with the first stages
+  __syncthreads();
+  if (tid < BT * 16) {
+    const int rl = tid >> 4, p = tid & 15;
+    if (st_row >= g.M) return;
+    const float lo = tile[rl][p], hi = tile[rl][p + 16];
+    kv_store<float, 1>(g.kv, st_row, st_dst, st_pos, seg, st_p, &lo, &hi, g.kv.rope_inv);
+  }
 }
 
 // ------------------------------------- fused projection, small widths
@@ -1242,19 +1369,12 @@ void pick_gemm(int M, int N, int K, bool kv, int hd, int num_cus, int* tile, int
 
 }  // namespace
 
-constexpr int kF32SplitK = 64;   // K per split of the fp32 GEMM
-
 // Rows from which the fused small-width projection is used: below, the K-split
 // two-product path spreads the weight reads over more workgroups.
 static int fused_min_rows() {
   const int64_t v = tuning(CO_TUNE_PROJECT_FUSED_MIN_ROWS);
   if (v >= 1) return v < INT32_MAX ? static_cast<int>(v) : INT32_MAX;
   return 4096;
-}
-
-static int f32_splits(int K) {
-  const int s = (K + kF32SplitK - 1) / kF32SplitK;
-  return s < 1 ? 1 : (s > 32 ? 32 : s);
 }
 
 ProjectPlan plan_project(int M, int Dcat, int d, int n_kv, int hd, int dtype, int num_cus) {
@@ -1266,14 +1386,13 @@ ProjectPlan plan_project(int M, int Dcat, int d, int n_kv, int hd, int dtype, in
     pick_gemm(M, d, Dcat, false, hd, num_cus, &p.f_tile, &p.f_split);
     pick_gemm(M, n_kv, d, true, hd, num_cus, &p.kv_tile, &p.kv_split);
   } else {
-    // fp32: K split in pieces of two 32-deep steps, so that few dependent load
-    // rounds lie on any workgroup's path (the shapes it serves are latency-bound)
-    p.f_tile = p.kv_tile = -1;
-    p.f_split = f32_splits(Dcat);
-    p.kv_split = f32_splits(d);
+    p.f_tile = p.kv_tile = -1;   // K is split inside a workgroup only
+    p.f_split = p.kv_split = 1;
   }
+  // fp32 keeps room for an unsplit K/V product whose epilogue normalises keys
   auto part = [&](int split, int N) -> size_t {
-    return (dtype == CO_DTYPE_F32 || split > 1) ? static_cast<size_t>(split) * M * N * 4 : 0;
+    return (split > 1 || (dtype == CO_DTYPE_F32 && N == n_kv)) ? static_cast<size_t>(split) * M * N * 4
+                                                               : 0;
   };
   p.z_bytes = (static_cast<size_t>(M) * d * es + 255) / 256 * 256;
   const size_t pf = part(p.f_split, d), pk = part(p.kv_split, n_kv);
@@ -1287,8 +1406,8 @@ bool route_foldable(const ProjectArgs& a, const ProjectPlan& p) {
   const bool sep = a.wfc != nullptr;
   const bool fused = !sep && a.znorm == nullptr && a.dst.knorm == nullptr && p.fused &&
                      (a.fe != nullptr || a.e == nullptr);
-  return a.dtype == CO_DTYPE_BF16 && a.M > 0 && !sep && !fused && p.f_tile < kWide &&
-         p.f_split == 1;
+  if (a.dtype == CO_DTYPE_F32) return a.M > 0 && !sep;
+  return a.M > 0 && !sep && !fused && p.f_tile < kWide && p.f_split == 1;
 }
 
 hipError_t launch_project(const ProjectArgs& a, const ProjectPlan& p, hipStream_t stream) {
@@ -1315,32 +1434,31 @@ hipError_t launch_project(const ProjectArgs& a, const ProjectPlan& p, hipStream_
   if (sep) f.e = nullptr;
 
   if (a.dtype == CO_DTYPE_F32) {
-    f.k_per_split = ((f.K + p.f_split - 1) / p.f_split + 31) / 32 * 32;
-    kv.k_per_split = ((kv.K + p.kv_split - 1) / p.kv_split + 31) / 32 * 32;
-    const int fs = (f.K + f.k_per_split - 1) / f.k_per_split;
-    const int ks = (kv.K + kv.k_per_split - 1) / kv.k_per_split;
-    f.mode = kv.mode = kModePartial;
-    const int64_t nz = static_cast<int64_t>(a.M) * a.d / 4;
+    f.mode = kModeZ;
+    if (a.route != nullptr) {
+      if (!route_foldable(a, p)) return hipErrorInvalidValue;   // the caller checks first
+      f.route = *a.route;
+      f.route_blocks = (a.route->S + kF32Waves - 1) / kF32Waves;
+    }
+    const int rows = (a.M + kF32Tile - 1) / kF32Tile;
+    const dim3 block(64 * kF32Waves);
     for (int pass = 0; pass < passes; ++pass) {
       if (pass == 1) f.B = a.wfc;
-      hipLaunchKernelGGL(gemm_f32_kernel, dim3((f.N + 63) / 64, (f.M + 31) / 32, fs), dim3(256),
-                         0, stream, f);
-      if (a.znorm != nullptr)
-        hipLaunchKernelGGL(epi_z_norm_kernel<float>, dim3(a.M), dim3(256), 0, stream, part, fs,
-                           a.M, a.d, static_cast<float*>(z), static_cast<const float*>(nullptr),
-                           static_cast<const float*>(nullptr), a.dst.row_dst, sep ? pass + 1 : 0,
-                           a.znorm);
-      else
-        hipLaunchKernelGGL(epi_z_kernel<float>, dim3(static_cast<unsigned>((nz + 255) / 256)),
-                           dim3(256), 0, stream, part, fs, a.M, a.d, static_cast<float*>(z),
-                           static_cast<const float*>(nullptr), static_cast<const float*>(nullptr),
-                           a.dst.row_dst, sep ? pass + 1 : 0);
+      f.z_rows = sep ? pass + 1 : 0;
+      hipLaunchKernelGGL(gemm_f32_kernel, dim3((f.N + kF32Tile - 1) / kF32Tile, rows + f.route_blocks),
+                         block, 0, stream, f);
     }
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((kv.N + 63) / 64, (kv.M + 31) / 32, ks), dim3(256),
-                       0, stream, kv);
-    const int64_t items = static_cast<int64_t>(a.M) * (n_kv / 2);
-    hipLaunchKernelGGL(epi_kv_kernel<float>, dim3(static_cast<unsigned>((items + 255) / 256)),
-                       dim3(256), 0, stream, part, ks, a.M, n_kv, a.dst);
+    if (a.znorm != nullptr)
+      hipLaunchKernelGGL(z_norm_kernel<float>, dim3(a.M), dim3(256), 0, stream,
+                         static_cast<float*>(z), a.M, a.d, a.znorm);
+    // keys are normalised over whole heads, by the epilogue over an unsplit product
+    kv.mode = a.dst.knorm != nullptr ? kModePartial : kModeKV;
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3(n_kv / kF32Tile, rows), block, 0, stream, kv);
+    if (a.dst.knorm != nullptr) {
+      const int64_t items = static_cast<int64_t>(a.M) * (n_kv / 2);
+      hipLaunchKernelGGL(epi_kv_kernel<float>, dim3(static_cast<unsigned>((items + 255) / 256)),
+                         dim3(256), 0, stream, part, 1, a.M, n_kv, a.dst);
+    }
     return hipGetLastError();
   }
 
