@@ -1088,7 +1088,14 @@ hipError_t launch_attention_backward(const BwdArgs& b, hipStream_t stream) {
 //   dJ_r = [R(pos_r)^T dk_r ; dv_r] for every layer and KV head (W_KV's row order),
 //   dW_KV += sum_r dJ_r z_r^T,   dz_r = W_KV^T dJ_r,
 //   dW_F  += sum_r dz_r h_r^T + u E^T,   dE += F^T u,   u = sum over carried r of dz_r.
-// The products run on the projection's MFMA kernels with the summed index (the
+// With x_r the row as projected (h_r, plus E where carried), Phi is linear, so
+// both weight gradients follow from one product over the rows:
+//   G = sum_r dJ_r x_r^T = dJ^T H + t E^T, t = sum over carried r of dJ_r,
+//   dW_F += W_KV^T G,   dW_KV += G W_F^T,   dE += W_F^T (W_KV^T t),
+// where the last three do not grow with the rows.  The shared-product path
+// below takes them in that order; the per-row path (small row counts against
+// wide weights, see the rule at launch_project_backward) forms z and dz.  Its
+// products run on the projection's MFMA kernels with the summed index (the
 // rows) contiguous in both operands, so the row-major inputs are transposed
 // first; rows are padded with zeros to a multiple of 256.
 namespace co {
@@ -1335,9 +1342,466 @@ __global__ __launch_bounds__(256) void pb_de_kernel(float* dep, const float* u, 
         (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
 }
 
+// ------------------------------------------------ shared-product path
+//
+// gather   dJ [Mp][NKV] in bf16 (rows past M zero) and, per 256 / (hd/8) rows,
+//          the sums of the carried rows' dJ in fp32
+// rows     G's split partials: dJ^T H over a range of rows, both operands
+//          row-major, read from LDS with transposing reads
+// sum      G = the sum of the splits, t = the sum of the partial sums
+// weights  dW_F, dW_KV (fp32 products: G keeps its 32 bits) and dE
+// Four launches and no transposed copies; bound by the reads of the rows and of
+// the gradient caches.  32768 rows, 768 -> 256 -> 256: 51 us a call, 161 us with
+// the per-row products (the whole training backward 823 -> 590 us).
+
+constexpr int kPbRowUnit = 64;    // rows per staged step of the row product
+constexpr int kPbTile = 128;      // its tile edge (NKV x Dcat)
+
+struct PbShared {
+  uint16_t* dj;                   // [Mp][NKV]
+  float *tpart, *t, *upart;       // [t_parts][NKV], [NKV], [NKV / 64][d]
+  float *part, *G;                // [splits][NKV][Dcat], [NKV][Dcat]
+  int Mp, t_parts, splits, rows_per;
+  size_t bytes;
+};
+
+PbShared pb_shared(void* ws, int M, int Dcat, int d, int n_kv, int hd, int num_cus) {
+  PbShared w{};
+  w.Mp = (M + kPbRowUnit - 1) / kPbRowUnit * kPbRowUnit;
+  const int rows_wg = 256 / (hd / 8);
+  w.t_parts = (w.Mp + rows_wg - 1) / rows_wg;
+  // about one workgroup per CU, each with at least four steps of rows
+  const int64_t tiles = static_cast<int64_t>(n_kv / kPbTile) * ((Dcat + kPbTile - 1) / kPbTile);
+  const int64_t units = w.Mp / kPbRowUnit;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(num_cus / tiles, units / 4));
+  w.rows_per = static_cast<int>((units + want - 1) / want) * kPbRowUnit;
+  w.splits = (w.Mp + w.rows_per - 1) / w.rows_per;
+  auto take = [&](int64_t bytes) {   // ws null: only the size is wanted
+    char* q = ws ? static_cast<char*>(ws) + w.bytes : nullptr;
+    w.bytes += static_cast<size_t>(pb_up(bytes));
+    return q;
+  };
+  const int64_t nk = n_kv;
+  w.dj = reinterpret_cast<uint16_t*>(take(static_cast<int64_t>(w.Mp) * nk * 2));
+  w.tpart = reinterpret_cast<float*>(take(w.t_parts * nk * 4));
+  w.t = reinterpret_cast<float*>(take(nk * 4));
+  w.upart = reinterpret_cast<float*>(take(nk / 64 * d * 4));
+  w.part = reinterpret_cast<float*>(take(w.splits > 1 ? w.splits * nk * Dcat * 4 : 0));
+  w.G = reinterpret_cast<float*>(take(nk * Dcat * 4));
+  return w;
+}
+
+// A workgroup takes 256 / (hd/8) rows and walks their layers and heads; hd/8
+// lanes hold a row's rotation pairs, four each, whose angles serve every head.
+// Key gradients and the dJ row move in 16- and 8-byte pieces; the value
+// gradients ([hd][16] per page) in 4-byte ones, whose lines the rows of a page
+// share in the workgroup.  Bound by the reads of the gradient caches.
+template <int HD>
+__global__ __launch_bounds__(256) void pb_gather_rows_kernel(ProjBwdArgs a, uint16_t* dj, int Mp,
+                                                             float* tpart) {
+  constexpr int LPR = HD / 8, RWG = 256 / LPR, half = HD / 2, RW = 64 / LPR;   // rows per wavefront
+  constexpr int64_t pe = static_cast<int64_t>(kPage) * HD;
+  __shared__ float red[4][2 * HD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int q = tid % LPR, i0 = 4 * q;
+  const int r = blockIdx.x * RWG + tid / LPR;
+  const int n_kv = 2 * a.L * a.Hkv * HD;
+  const int32_t dst = r < a.M ? a.row_dst[r] : kSkip;
+  const bool carried = dst < 0 && dst != kSkip;
+  // page of layer 0, head 0, and the distance to the next layer's; -1: no gradient
+  int64_t pg0 = -1, lstep = 0;
+  int slot = 0;
+  const float *kb = a.dk, *vb = a.dv;
+  if (dst >= 0) {
+    const int page = dst / kPage;
+    slot = dst % kPage;
+    if (page < a.num_pages) pg0 = static_cast<int64_t>(page) * a.Hkv;
+    lstep = static_cast<int64_t>(a.num_pages) * a.Hkv;
+  } else if (carried) {
+    const int c = -1 - dst, s = r / a.B;
+    slot = c % kPage;
+    if (c < a.CP * kPage) pg0 = (static_cast<int64_t>(s) * a.CP + c / kPage) * a.Hkv;
+    lstep = static_cast<int64_t>(a.S) * a.CP * a.Hkv;
+    kb = a.dkc;
+    vb = a.dvc;
+  }
+  float cs[4], sn[4];
+  const int pos = r < a.M ? a.row_pos[r] : 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) rope_cos_sin(pos, a.rope_inv[i0 + e], &cs[e], &sn[e]);
+  const bool any_carried = __any(carried && pg0 >= 0);
+  for (int l = 0; l < a.L; ++l)
+    for (int g = 0; g < a.Hkv; ++g) {
+      f32x4 klo = {0.f, 0.f, 0.f, 0.f}, khi = klo, vlo = klo, vhi = klo;
+      if (pg0 >= 0) {
+        const int64_t pg = pg0 + l * lstep + g;
+        const float* kr = kb + pg * pe + slot * HD + i0;
+        const float* vr = vb + pg * pe + i0 * kPage + slot;
+        float k0[4], k1[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          k0[e] = kr[e];
+          k1[e] = kr[e + half];
+          vlo[e] = vr[e * kPage];
+          vhi[e] = vr[(e + half) * kPage];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {   // R^T: turn back by the row's angle
+          klo[e] = k0[e] * cs[e] + k1[e] * sn[e];
+          khi[e] = k1[e] * cs[e] - k0[e] * sn[e];
+        }
+      }
+      const int jk = (2 * l * a.Hkv + g) * HD, jv = ((2 * l + 1) * a.Hkv + g) * HD;
+      if (r < Mp) {
+        uint16_t* row = dj + static_cast<int64_t>(r) * n_kv + i0;
+        u16x4 o0, o1, o2, o3;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o0[e] = f2bf(klo[e]);
+          o1[e] = f2bf(khi[e]);
+          o2[e] = f2bf(vlo[e]);
+          o3[e] = f2bf(vhi[e]);
+        }
+        *reinterpret_cast<u16x4*>(row + jk) = o0;
+        *reinterpret_cast<u16x4*>(row + jk + half) = o1;
+        *reinterpret_cast<u16x4*>(row + jv) = o2;
+        *reinterpret_cast<u16x4*>(row + jv + half) = o3;
+      }
+      // the carried rows' sums: over the wavefront's rows, then the wavefronts
+      f32x4 sums[4] = {klo, khi, vlo, vhi};
+      if (any_carried) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float v = carried ? sums[x][e] : 0.f;
+#pragma unroll
+            for (int o = LPR; o < 64; o <<= 1) v += __shfl_xor(v, o);
+            sums[x][e] = v;
+          }
+      } else {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sums[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      __syncthreads();   // the sums of the head before are read
+      if (lane < LPR) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          *reinterpret_cast<f32x4*>(&red[wave][x * half + i0]) = sums[x];
+      }
+      __syncthreads();
+      if (tid < 2 * HD) {
+        const int j = tid < HD ? jk + tid : jv + tid - HD;
+        tpart[static_cast<int64_t>(blockIdx.x) * n_kv + j] =
+            (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+      }
+    }
+}
+
+// Partial of C[m][n] = sum over rows r of A[r][m] B[r][n] (bf16, row-major): a
+// 128 x 128 tile over rows_per rows per workgroup of eight wavefronts.  A stage
+// of 64 rows of both operands (32 KiB) comes in by direct-to-LDS loads, three
+// stages ahead; wavefront w takes the 64 x 64 block (w / 2) % 2, w % 2 over one
+// half (w / 4) of the stage's rows, and the halves are added through LDS at the
+// end, so that two wavefronts share each SIMD.  The operands run along m and n
+// in LDS and are turned by ds_read_b64_tr_b16; a row's four 64-byte blocks are
+// XOR-permuted by (row % 4), so that the 32 lanes of a pass, four rows of 64
+// bytes, cover all 64 banks.  A has rows up to a multiple of 64 (zero past M),
+// B's rows past M repeat the last one.
+__global__ __launch_bounds__(512, 2) void pb_rows_kernel(const uint16_t* A, int lda,
+                                                         const uint16_t* B, int ldb, int M, int Mp,
+                                                         int N, int rows_per, int tiles_n, int total,
+                                                         float* part) {
+  constexpr int T = kPbTile, BK = kPbRowUnit, ROWB = T * 2, OPB = BK * ROWB, STAGE = 2 * OPB;
+  constexpr int NS = 4, LPW = STAGE / 1024 / 8;   // stages; 1 KiB loads per wavefront per stage
+  static_assert(NS * STAGE <= 160 * 1024 && 4 * 64 * 64 * 4 <= NS * STAGE, "LDS");
+  __shared__ __align__(16) unsigned char smem[NS * STAGE];
+  // consecutive tiles of one row range, which share its operand rows, run on
+  // one XCD (workgroup ids are dealt to the 8 XCDs in turn)
+  const int per = gridDim.x >> 3, t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (t >= total) return;
+  const int tiles = lda / T * tiles_n, sp = t / tiles, tt = t % tiles;
+  const int m0 = tt / tiles_n * T, n0 = tt % tiles_n * T;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  const int r0 = sp * rows_per, nk = (min(Mp, r0 + rows_per) - r0) / BK;
+  const uint32_t ring = lds_addr(smem);
+
+  // load j of this wavefront: rows 4 (wave LPW + j) .. + 3 of A, then of B
+  int lrow[LPW], lcol[LPW];
+#pragma unroll
+  for (int j = 0; j < LPW; ++j) {
+    const int blk = wave * LPW + j;
+    lrow[j] = blk % (BK / 4) * 4 + (lane >> 4);
+    const int ch = lane & 15;   // physical 16-byte chunk; its 64-byte block is permuted
+    lcol[j] = (((ch >> 2) ^ (lrow[j] & 3)) << 2 | (ch & 3)) * 8;
+  }
+  auto issue = [&](int kt) {
+    const uint32_t st = ring + (kt % NS) * STAGE;
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+      const int blk = wave * LPW + j, row = r0 + kt * BK + lrow[j];
+      const uint16_t* src =
+          blk < BK / 4 ? A + static_cast<int64_t>(row) * lda + m0 + lcol[j]
+                       : B + static_cast<int64_t>(min(row, M - 1)) * ldb + min(n0 + lcol[j], N - 8);
+      lds_dma16_opaque(src, st + blk * 1024);
+    }
+  };
+  // this lane's source in the transposing reads: k row, element block
+  const int h = lane >> 5, kr = 8 * h + ((lane >> 2) & 3), el = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  auto frag = [&](const unsigned char* op, int k16, int col0) {
+    const int col = col0 + el, rr = 16 * k16 + kr;   // rr and rr + 4 have the same rr % 4
+    const int off = (((col >> 5) ^ (rr & 3)) << 6) + (col & 31) * 2;
+    return lds_read_tr(op + rr * ROWB + off, op + (rr + 4) * ROWB + off);
+  };
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < nk) issue(s);
+  for (int kt = 0; kt < nk; ++kt) {
+    const int ahead = min(NS - 2, nk - 1 - kt);
+    if (ahead >= 2) wait_vm_lgkm_barrier<2 * LPW>();
+    else if (ahead == 1) wait_vm_lgkm_barrier<LPW>();
+    else wait_vm_lgkm_barrier<0>();
+    if (kt + NS - 1 < nk) issue(kt + NS - 1);   // into the slot of stage kt - 1, read by all
+    const unsigned char* st = smem + (kt % NS) * STAGE;
+#pragma unroll
+    for (int s = 0; s < BK / 32; ++s) {
+      const int k16 = kh * (BK / 32) + s;
+      u16x8 fa[2], fb[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        fa[x] = frag(st, k16, wm * 64 + x * 32);
+        fb[x] = frag(st + OPB, k16, wn * 64 + x * 32);
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = mfma32x32x16(fa[x], fb[y], acc[x][y]);
+    }
+  }
+  wait_vm_lgkm_barrier<0>();   // the ring is free
+  float* sc = reinterpret_cast<float*>(smem) + (wave & 3) * 4096 + lane;
+  if (kh == 1) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[((x * 2 + y) * 16 + r) * 64] = acc[x][y][r];
+  }
+  __syncthreads();
+  if (kh == 1) return;
+  float* out = part + static_cast<int64_t>(sp) * lda * N;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int col = n0 + wn * 64 + y * 32 + (lane & 31);
+      if (col >= N) continue;   // the last tile of a Dcat that is 64 past a multiple of 128
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = m0 + wm * 64 + x * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        out[static_cast<int64_t>(row) * N + col] = acc[x][y][r] + sc[((x * 2 + y) * 16 + r) * 64];
+      }
+    }
+}
+
+// Workgroups 0 .. n_kv/64 - 1: t[j] = the sum of its partial sums, sixteen
+// interleaved series added in order, then these 64 rows' part of u = W_KV^T t.
+// The rest: G, four elements per thread (splits in order).
+__global__ __launch_bounds__(1024) void pb_sum_kernel(const float* part, int splits, int64_t n,
+                                                      float* G, const float* tpart, int t_parts,
+                                                      int n_kv, float* t, const uint16_t* wkv,
+                                                      int d, float* upart) {
+  __shared__ float red[16][64], sum[64], ured[16][64];
+  const int tid = threadIdx.x, tb = n_kv / 64;
+  if (static_cast<int>(blockIdx.x) < tb) {
+    const int j = blockIdx.x * 64 + (tid & 63), w = tid >> 6;
+    float v = 0.f;
+#pragma unroll 16
+    for (int p = w; p < t_parts; p += 16) v += tpart[static_cast<int64_t>(p) * n_kv + j];
+    red[w][tid & 63] = v;
+    __syncthreads();
+    if (w == 0) {
+#pragma unroll
+      for (int k = 1; k < 16; ++k) v += red[k][tid];
+      t[j] = v;
+      sum[tid] = v;
+    }
+    __syncthreads();
+    for (int d0 = 0; d0 < d; d0 += 64) {   // wavefront w: rows 4w .. 4w + 3, lane: column
+      float x = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        x = fmaf(bf2f(wkv[static_cast<int64_t>(blockIdx.x * 64 + 4 * w + k) * d + d0 + (tid & 63)]),
+                 sum[4 * w + k], x);
+      ured[w][tid & 63] = x;
+      __syncthreads();
+      if (w == 0) {
+#pragma unroll
+        for (int k = 1; k < 16; ++k) x += ured[k][tid];
+        upart[static_cast<int64_t>(blockIdx.x) * d + d0 + tid] = x;
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  const int64_t i = (static_cast<int64_t>(blockIdx.x - tb) * 1024 + tid) * 4;
+  if (i >= n) return;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  int s = 0;
+  for (; s + 8 <= splits; s += 8) {   // eight loads in flight
+    f32x4 x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const f32x4*>(part + (s + k) * n + i);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += x[k];
+  }
+  for (; s < splits; ++s) v += *reinterpret_cast<const f32x4*>(part + s * n + i);
+  *reinterpret_cast<f32x4*>(G + i) = v;
+}
+
+// dW_F += W_KV^T G', dW_KV += G' W_F^T with G' = G + t E^T, and dE += W_F^T u.  A 32 x 32 output tile per workgroup of sixteen wavefronts on
+// v_mfma_f32_32x32x2_f32, the summed index split over the wavefronts and added
+// in LDS in order (the widths are a few hundred: latency is what counts); then
+// one workgroup per 64 columns of dE.
+__global__ __launch_bounds__(1024) void pb_weights_kernel(ProjBwdArgs a, const float* G,
+                                                          const float* t, const float* upart,
+                                                          int n_kv, int nf, int nkv) {
+  constexpr int W = 16;
+  __shared__ float sc[W][1024];
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = a.d, Dcat = a.Dcat, b = blockIdx.x;
+  const uint16_t* wf = static_cast<const uint16_t*>(a.wf);
+  const uint16_t* wkv = static_cast<const uint16_t*>(a.wkv);
+  const uint16_t* E = static_cast<const uint16_t*>(a.e);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  if (b < nf) {   // dW_F tile: rows dd of d, columns c of Dcat, summed over j < n_kv
+    const int m0 = b / (Dcat / 32) * 32, n0 = b % (Dcat / 32) * 32;
+    const float ec = bf2f(E[n0 + r32]);
+    const int per = n_kv / W, j0 = wave * per;   // n_kv is a multiple of 128: per of 8
+#pragma unroll 2
+    for (int j = j0; j < j0 + per; j += 8) {
+      float x[4], y[4], tj[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int jj = j + 2 * i + h;
+        x[i] = bf2f(wkv[static_cast<int64_t>(jj) * d + m0 + r32]);
+        y[i] = G[static_cast<int64_t>(jj) * Dcat + n0 + r32];
+        tj[i] = t[jj];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = mfma32x32x2_f32(x[i], fmaf(tj[i], ec, y[i]), acc);
+    }
+  } else if (b < nf + nkv) {   // dW_KV tile: rows j of n_kv, columns dd of d, summed over Dcat
+    const int m0 = (b - nf) / (d / 32) * 32, n0 = (b - nf) % (d / 32) * 32;
+    const float tj = t[m0 + r32];
+    const float* gr = G + static_cast<int64_t>(m0 + r32) * Dcat + 4 * h;
+    const uint16_t* wr = wf + static_cast<int64_t>(n0 + r32) * Dcat + 4 * h;
+    const int U = Dcat / 8, u0 = U * wave / W, u1 = U * (wave + 1) / W;
+#pragma unroll 4
+    for (int u = u0; u < u1; ++u) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(gr + u * 8);
+      const u16x4 y = *reinterpret_cast<const u16x4*>(wr + u * 8);
+      const u16x4 ev = *reinterpret_cast<const u16x4*>(E + u * 8 + 4 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = mfma32x32x2_f32(fmaf(tj, bf2f(ev[e]), x[e]), bf2f(y[e]), acc);
+    }
+  } else {   // dE: u, 1024 rows at a time, then this workgroup's 64 columns
+    const int c = (b - nf - nkv) * 64 + lane;
+    float v = 0.f;
+    for (int d0 = 0; d0 < d; d0 += 1024) {
+      const int nd = min(1024, d - d0);   // a multiple of 64
+      if (tid < nd) {
+        float x = 0.f;
+        for (int p = 0; p < n_kv / 64; ++p) x += upart[static_cast<int64_t>(p) * d + d0 + tid];
+        sc[W - 1][tid] = x;
+      }
+      __syncthreads();
+#pragma unroll 8
+      for (int k = wave; k < nd; k += W)
+        v = fmaf(bf2f(wf[static_cast<int64_t>(d0 + k) * Dcat + c]), sc[W - 1][k], v);
+      __syncthreads();
+    }
+    sc[wave][lane] = v;
+    __syncthreads();
+    if (wave == 0) {
+      for (int k = 1; k < W; ++k) v += sc[k][lane];
+      a.de[c] += v;
+    }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sc[wave][(8 * (r >> 2) + 4 * h + (r & 3)) * 32 + r32] = acc[r];
+  __syncthreads();
+  float v = sc[0][tid];
+#pragma unroll
+  for (int w = 1; w < W; ++w) v += sc[w][tid];
+  const int row = tid >> 5, col = tid & 31;
+  if (b < nf) {
+    const int m0 = b / (Dcat / 32) * 32, n0 = b % (Dcat / 32) * 32;
+    a.dwf[static_cast<int64_t>(m0 + row) * Dcat + n0 + col] += v;
+  } else {
+    const int m0 = (b - nf) / (d / 32) * 32, n0 = (b - nf) % (d / 32) * 32;
+    a.dwkv[static_cast<int64_t>(m0 + row) * d + n0 + col] += v;
+  }
+}
+
+// Whether the shared product is the cheaper way.  Its work per row is
+// 2 NKV Dcat operations against 4 d (Dcat + NKV), but it adds fp32 products of
+// 4 d NKV Dcat operations whatever the row count.  The constants (seconds with
+// the launches, operations a second) fit both paths measured over each other's
+// range, rows x Dcat x d x NKV, shared against per-row:
+//   32768 x 768 x 256 x 256     51 /  161 us     512 x 2560 x 1024 x 1024   250 / 109 us
+//   2048 x 768 x 256 x 256      30 /   72 us    8192 x 2560 x 1024 x 1024   313 / 259 us
+//   64 x 768 x 256 x 256        25 /   62 us   32768 x 2560 x 1024 x 1024   581 / 766 us
+//                                               4096 x 8192 x 2048 x 2048  2937 / 548 us
+bool pb_use_shared(int M, int Dcat, int d, int n_kv) {
+  const double m = M, k = Dcat, n = n_kv, w = d;
+  const double shared = 25e-6 + m * 2 * n * k / 5e14 + 4 * w * n * k / 5e13;
+  const double per_row = 62e-6 + m * 4 * w * (k + n) / 7e14;
+  return shared < per_row;
+}
+
+hipError_t launch_shared(const ProjBwdArgs& a, int n_kv, hipStream_t stream) {
+  const PbShared w = pb_shared(a.ws, a.M, a.Dcat, a.d, n_kv, a.hd, a.num_cus);
+  if (a.hd == 64)
+    hipLaunchKernelGGL(pb_gather_rows_kernel<64>, dim3(w.t_parts), dim3(256), 0, stream, a, w.dj,
+                       w.Mp, w.tpart);
+  else
+    hipLaunchKernelGGL(pb_gather_rows_kernel<128>, dim3(w.t_parts), dim3(256), 0, stream, a, w.dj,
+                       w.Mp, w.tpart);
+  const int tiles_n = (a.Dcat + kPbTile - 1) / kPbTile;
+  const int total = n_kv / kPbTile * tiles_n * w.splits;
+  hipLaunchKernelGGL(pb_rows_kernel, dim3((total + 7) / 8 * 8), dim3(512), 0, stream, w.dj, n_kv,
+                     static_cast<const uint16_t*>(a.hidden), a.Dcat, a.M, w.Mp, a.Dcat, w.rows_per,
+                     tiles_n, total, w.splits > 1 ? w.part : w.G);
+  const int64_t n = static_cast<int64_t>(n_kv) * a.Dcat;
+  const int64_t sums = w.splits > 1 ? (n / 4 + 1023) / 1024 : 0;
+  hipLaunchKernelGGL(pb_sum_kernel, dim3(static_cast<unsigned>(n_kv / 64 + sums)), dim3(1024), 0,
+                     stream, w.part, w.splits, n, w.G, w.tpart, w.t_parts, n_kv, w.t,
+                     static_cast<const uint16_t*>(a.wkv), a.d, w.upart);
+  const int nf = a.d / 32 * (a.Dcat / 32), nkv = n_kv / 32 * (a.d / 32);
+  hipLaunchKernelGGL(pb_weights_kernel, dim3(nf + nkv + a.Dcat / 64), dim3(1024), 0, stream, a, w.G,
+                     w.t, w.upart, n_kv, nf, nkv);
+  return hipGetLastError();
+}
+
 }  // namespace
 
-size_t proj_bwd_ws_bytes(int M, int Dcat, int d, int n_kv, int num_cus) {
+size_t proj_bwd_ws_bytes(int M, int Dcat, int d, int n_kv, int hd, int num_cus) {
+  if (pb_use_shared(M, Dcat, d, n_kv)) return pb_shared(nullptr, M, Dcat, d, n_kv, hd, num_cus).bytes;
   const int64_t Mp = (M + kRowPad - 1) / kRowPad * kRowPad;
   size_t part = gemm_acc_ws_bytes(d, M, Dcat, num_cus);
   part = std::max(part, gemm_acc_ws_bytes(n_kv, d, static_cast<int>(Mp), num_cus));
@@ -1355,7 +1819,8 @@ hipError_t launch_project_backward(const ProjBwdArgs& a, hipStream_t stream) {
   const int n_kv = 2 * a.L * a.Hkv * a.hd;
   // every transpose below has C, Rp and both leading dimensions multiples of 64
   // (Dcat and d are, Mp is a multiple of 256, NKV of 128)
-  if (a.Dcat % 64 || a.d % 64 || n_kv % 64) return hipErrorInvalidValue;
+  if (a.Dcat % 64 || a.d % 64 || n_kv % 128) return hipErrorInvalidValue;
+  if (pb_use_shared(a.M, a.Dcat, a.d, n_kv)) return launch_shared(a, n_kv, stream);
   const PbWs w = pb_ws(a.ws, a.M, a.Dcat, a.d, n_kv);
   const int Mp = w.Mp;
   hipError_t err;

@@ -303,7 +303,7 @@ size_t carryover_workspace_bytes(const co_dims* dims, int32_t which) {
       return dims->dtype == CO_DTYPE_BF16
                  ? proj_bwd_ws_bytes(dims->num_seqs * dims->block, dims->feat_dim, dims->model_dim,
                                      2 * dims->num_layers * dims->num_kv_heads * dims->head_dim,
-                                     num_cus())
+                                     dims->head_dim, num_cus())
                  : 0;
     case CO_WS_ATTENTION_BACKWARD:
       return bwd_workspace_bytes(dims->num_seqs, dims->num_layers, dims->num_kv_heads,

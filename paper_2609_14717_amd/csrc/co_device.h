@@ -126,6 +126,20 @@ __device__ __forceinline__ f32x16 mfma32x32x2_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
+// One operand of v_mfma_f32_32x32x16_bf16 out of LDS rows that run along the
+// other dimension (rows of k, 16-bit elements along m): two ds_read_b64_tr_b16,
+// each of which turns a 4 (k) x 16 (m) block per sixteen lanes.  Lane l of a
+// sixteen supplies the address of k row (l / 4) % 4, elements 4 (l % 4) .. + 3,
+// and receives the four k of element l % 16.  p0 and p1: this lane's addresses
+// in the k blocks 0-3 and 4-7 of its half's eight.
+__device__ __forceinline__ u16x8 lds_read_tr(const unsigned char* p0, const unsigned char* p1) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_v4;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p0));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(p1));
+  return __builtin_bit_cast(u16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // Rotary angle of pair index i at position pos: pos * theta^(-2i/hd).  The product
 // and the reduction to [-pi, pi] are done in fp64 so that positions of 10^5 keep
 // fp32 accuracy after the reduction; sin/cos are then taken in fp32.

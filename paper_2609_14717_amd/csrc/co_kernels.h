@@ -153,7 +153,7 @@ struct ProjBwdArgs {
   void* ws;
 };
 
-size_t proj_bwd_ws_bytes(int M, int Dcat, int d, int n_kv, int num_cus);
+size_t proj_bwd_ws_bytes(int M, int Dcat, int d, int n_kv, int hd, int num_cus);
 hipError_t launch_project_backward(const ProjBwdArgs& p, hipStream_t stream);
 
 // Attention mass on the carried rows, from a finished attention call's LSE.

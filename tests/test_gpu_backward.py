@@ -496,3 +496,70 @@ def test_backward_direct_kv_train_full_size():
     dO = seq_block(w, wl.spec_dout(w, S=V), 1, sample)
     check(co, vdims, vst, q, out, lse, dO_dev, A, ost, Q, dO, w, sample, lambda v: v // A,
           {R: R * A}, tag="direct train", floor=FLOOR_UNIT)
+
+
+# (S, B, Dcat, d, L, Hkv, hd): row counts around the staged 64, one and several
+# row ranges, a Dcat that ends half a tile in, both head widths, several layers;
+# the last takes the per-row products (few rows against wide weights)
+PB_CASES = [(1, 1, 64, 64, 1, 1, 64), (3, 21, 320, 128, 1, 1, 64), (5, 13, 448, 192, 2, 1, 128),
+            (1, 700, 256, 320, 1, 4, 64), (40, 16, 768, 256, 1, 2, 64), (9, 200, 1024, 64, 3, 2, 128),
+            (2, 16, 4096, 2048, 1, 8, 64)]
+
+
+@pytest.mark.parametrize("c", PB_CASES, ids=lambda c: "-".join(map(str, c)))
+def test_projection_backward_products(c):
+    """dW_F, dW_KV and dE against 64-bit products for rows that are committed,
+    carried, skipped or point outside the caches, added to what the outputs
+    hold.  dJ, and on the per-row path z and dz, are rounded to bf16: at most
+    three relative errors of 2^-9 in every term."""
+    import paper_2609_14717_amd as co
+    S, B, Dcat, d, L, Hkv, hd = c
+    print(f"[backward] projection products {c}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(S * 1000 + B)
+    rnd = lambda *s, dt=torch.float32: torch.randn(s, generator=g, device="cuda").to(dt)  # noqa: E731
+    M, CP, P = S * B, (B + 15) // 16, (S * B + 15) // 16 + 3
+    n_kv = 2 * L * Hkv * hd
+    dims = co.make_dims(S, B, Dcat, d, L, Hkv, Hkv, hd, P, P, "bf16", 1e4)
+    wf, wkv, e = (rnd(*s, dt=torch.bfloat16) for s in ((d, Dcat), (n_kv, d), (Dcat,)))
+    h = rnd(S, B, Dcat, dt=torch.bfloat16)
+    dk, dv = rnd(L, P, Hkv, 16, hd), rnd(L, P, Hkv, hd, 16)
+    dkc, dvc = rnd(L, S, CP, Hkv, 16, hd), rnd(L, S, CP, Hkv, hd, 16)
+    kind = torch.randint(0, 4, (M,), generator=g, device="cuda")   # 0, 1 committed, 2 carried, 3 skipped
+    r, j = torch.arange(M, device="cuda"), torch.arange(M, device="cuda") % B
+    slot = torch.randperm(P * 16, generator=g, device="cuda")[:M]
+    dst = torch.where(kind < 2, slot, torch.where(kind == 2, -1 - j, torch.full_like(r, co.SKIP)))
+    if M > 8:
+        dst[3], dst[7] = P * 16 + 5, -1 - CP * 16              # outside the caches: no gradient
+    pos = torch.randint(0, 30000, (M,), generator=g, device="cuda")
+    rt = dict(accept_len=torch.zeros(S, dtype=torch.int32, device="cuda"),
+              row_pos=pos.to(torch.int32).view(S, B).contiguous(),
+              row_dst=dst.to(torch.int32).view(S, B).contiguous())
+    outs = [rnd(d, Dcat), rnd(n_kv, d), rnd(Dcat)]
+    want = [o.double().clone() for o in outs]
+    ws = torch.full((max(256, co.workspace_bytes(dims, co.CO_WS_PROJECT_BACKWARD)),), 255,
+                    dtype=torch.uint8, device="cuda")          # NaN patterns
+    co.carryover_project_kv_backward(dims, co.weights(wf, wkv, e), h, rt, dk, dv, dkc, dvc, *outs, ws)
+    torch.cuda.synchronize()
+
+    com, car = (dst >= 0) & (dst < P * 16), (dst < 0) & (dst >= -CP * 16)
+    gk, gv = (torch.zeros((M, L, Hkv, hd), dtype=torch.float64, device="cuda") for _ in range(2))
+    at = dst[com]
+    gk[com] = dk[:, at // 16, :, at % 16].double()
+    gv[com] = dv.permute(0, 1, 2, 4, 3)[:, at // 16, :, at % 16].double()
+    at, s = -1 - dst[car], r[car] // B
+    gk[car] = dkc[:, s, at // 16, :, at % 16].double()
+    gv[car] = dvc.permute(0, 1, 2, 3, 5, 4)[:, s, at // 16, :, at % 16].double()
+    i = torch.arange(hd // 2, device="cuda", dtype=torch.float64)
+    ang = pos.double()[:, None] * 1e4 ** (-2 * i / hd)
+    cs, sn = torch.cos(ang)[:, None, None], torch.sin(ang)[:, None, None]
+    lo, hi = gk[..., :hd // 2], gk[..., hd // 2:]
+    gk = torch.cat((lo * cs + hi * sn, hi * cs - lo * sn), -1)
+    dj = torch.stack((gk, gv), 2).reshape(M, n_kv)
+    carried = ((dst < 0) & (dst != co.SKIP)).double()[:, None]
+    x = h.view(M, Dcat).double() + carried * e.double()
+    G = dj.T @ x
+    add = [wkv.double().T @ G, G @ wf.double().T, ((carried * dj).sum(0) @ wkv.double()) @ wf.double()]
+    for name, o, w0, a in zip(("dW_F", "dW_KV", "dE"), outs, want, add):
+        err = float((o.double() - w0 - a).norm() / (a.norm() + 1e-30)) if float(a.norm()) else 0.0
+        print(f"  {name}: {err:.2e}", flush=True)
+        assert err <= 3 * 2.0 ** -9, (name, err)
