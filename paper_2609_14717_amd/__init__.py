@@ -300,7 +300,7 @@ def carryover_round(dims, w, hidden, draft_tok, target_tok, q, st, rt, out, lse,
                                  _stream(stream)), "carryover_round")
 
 
-NOALLOC_SCRATCH_BYTES = 128 << 20
+NOALLOC_SCRATCH_BYTES = 136 << 20
 
 
 def carryover_round_noalloc(dims, w, hidden, draft_tok, target_tok, q, st, rt, out, lse, flags,

@@ -455,6 +455,24 @@ __device__ __forceinline__ float* slot_ptr(const AttnArgs& a, int hdr_floats, in
   return a.ws + hdr_floats + slot * nqp * (a.hd + a.rec_sums);
 }
 
+// XOR keys of the 16-byte chunks of a tile in LDS (64 banks of 4 bytes: the
+// sixteen lanes of a pass must fall on sixteen 16-byte bank groups).
+//   Key rows of 128 bytes (head_dim 64) leave half of the 256-byte bank window to
+//   the row's parity and eight chunks to the key; rows of 256 bytes, sixteen.
+//   attn_bf16_kernel's lanes read slots {0-3, 8-11} (or {4-7, 12-15}) of both
+//   pages, Tile32's the sixteen slots of one page.
+//   Value rows are 32 bytes (a dim's sixteen slots): dims eight apart meet in the
+//   same banks, so every other eight dims swap their two chunks.
+template <int HD>
+__device__ __forceinline__ int swz_key_pair(int page, int slot) {
+  return HD == 64 ? ((slot >> 1) & 1) | (((slot >> 3) & 1) << 1) | (page << 2) : slot ^ (page << 2);
+}
+template <int HD>
+__device__ __forceinline__ int swz_key_page(int slot) {
+  return HD == 64 ? slot >> 1 : slot;
+}
+__device__ __forceinline__ int swz_value(int dim) { return (dim >> 3) & 1; }
+
 // The block's own rows (drafter_block_attention_ext) as 32-key tiles of a
 // (layer, KV head, sequence): rows t0 .. t0 + 31 of k_self / v_self
 // [layers][S][B][Hkv][HD] are loaded by the wavefront as lane jobs (keys: a row
@@ -504,17 +522,17 @@ struct SelfRows {
         x8[e] = f2bf(x * cs - y * sn);
         y8[e] = f2bf(y * cs + x * sn);
       }
-      const int rp = r & 15;
+      const int rp = r & 15, x = swz_key_pair<HD>(r >> 4, rp);
       unsigned char* kpg = slot + (r >> 4) * PAGE_BYTES + rp * ROWB;
-      *reinterpret_cast<u16x8*>(kpg + ((c ^ (rp & (CPR - 1))) << 4)) = x8;
-      *reinterpret_cast<u16x8*>(kpg + (((c + CPR / 2) ^ (rp & (CPR - 1))) << 4)) = y8;
+      *reinterpret_cast<u16x8*>(kpg + ((c ^ x) << 4)) = x8;
+      *reinterpret_cast<u16x8*>(kpg + (((c + CPR / 2) ^ x) << 4)) = y8;
     }
 #pragma unroll
     for (int i = 0; i < VJ; ++i) {
       const int jb = lane + 64 * i, r = jb / CPR, c = jb % CPR;
       uint16_t* vpg = reinterpret_cast<uint16_t*>(slot + (2 + (r >> 4)) * PAGE_BYTES);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) vpg[(c * 8 + e) * kPage + (r & 15)] = v8[i][e];
+      for (int e = 0; e < 8; ++e) vpg[(c * 8 + e) * kPage + ((r & 15) ^ (swz_value(c * 8) << 3))] = v8[i][e];
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes
   }
@@ -561,10 +579,10 @@ __device__ void self_rows_place(const unsigned char* raw, unsigned char* slot, i
       x8[e] = f2bf(x * cs - y * sn);
       y8[e] = f2bf(y * cs + x * sn);
     }
-    const int rp = r & 15;
+    const int rp = r & 15, x = swz_key_page<HD>(rp);
     unsigned char* kpg = slot + (r >> 4) * PAGE_BYTES + rp * ROWB;
-    *reinterpret_cast<u16x8*>(kpg + ((c ^ (rp & (CPR - 1))) << 4)) = x8;
-    *reinterpret_cast<u16x8*>(kpg + (((c + CPR / 2) ^ (rp & (CPR - 1))) << 4)) = y8;
+    *reinterpret_cast<u16x8*>(kpg + ((c ^ x) << 4)) = x8;
+    *reinterpret_cast<u16x8*>(kpg + (((c + CPR / 2) ^ x) << 4)) = y8;
   }
 #pragma unroll 2
   for (int i = 0; i < VJ; ++i) {
@@ -572,7 +590,7 @@ __device__ void self_rows_place(const unsigned char* raw, unsigned char* slot, i
     const u16x8 v8 = *reinterpret_cast<const u16x8*>(rv + r * ROWB + c * 16);
     uint16_t* vpg = reinterpret_cast<uint16_t*>(slot + (2 + (r >> 4)) * PAGE_BYTES);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) vpg[(c * 8 + e) * kPage + (r & 15)] = v8[e];
+    for (int e = 0; e < 8; ++e) vpg[(c * 8 + e) * kPage + ((r & 15) ^ (swz_value(c * 8) << 3))] = v8[e];
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes
 }
@@ -603,7 +621,6 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
   constexpr int QLD = HD + 8;              // padded LDS row of rotated queries (bf16)
   constexpr int QSZ = NQP * QLD;
   constexpr int ROWB = HD * 2;             // bytes of one key row
-  constexpr int CPR = ROWB / 16;           // 16-byte chunks per key row
   constexpr int PAGE_BYTES = kPage * ROWB; // one page of K (or of V)
   constexpr int LPP = PAGE_BYTES / 1024;   // 1 KiB wave loads per page
   constexpr int TILE_BYTES = 4 * PAGE_BYTES;   // K page 0, K page 1, V page 0, V page 1
@@ -658,14 +675,16 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
   const int slot_base = (grp & 1) * 8;
   unsigned char* my_ring = smem + wave * NS * TILE_BYTES;
   // Per-lane source offsets (elements) of the direct-to-LDS loads of one page:
-  // K rows land XOR-swizzled by (row mod CPR), V pages are copied as they are.
-  int k_off[LPP], v_off[LPP];
+  // chunks land XOR-permuted (page 1's keys differ from page 0's by chunk 4).
+  int k_off[2][LPP], v_off[LPP];
 #pragma unroll
   for (int q = 0; q < LPP; ++q) {
     const int byte = q * 1024 + lane * 16;
     const int r = byte / ROWB, pch = (byte % ROWB) / 16;
-    k_off[q] = r * HD + (pch ^ (r & (CPR - 1))) * 8;
-    v_off[q] = byte / 2;
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+      k_off[half][q] = r * HD + (pch ^ swz_key_pair<HD>(half, r)) * 8;
+    v_off[q] = (byte ^ (swz_value(byte / 32) << 4)) / 2;
   }
   // LDS byte offsets (within a tile) of this lane's K and V fragments
   uint32_t ka_off[KS], kb_off[KS], v_frag_off;
@@ -674,10 +693,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int ch = ks * 4 + grp;
-      ka_off[ks] = (key_a >> 4) * PAGE_BYTES + ra_ * ROWB + ((ch ^ (ra_ & (CPR - 1))) << 4);
-      kb_off[ks] = (key_b >> 4) * PAGE_BYTES + rb_ * ROWB + ((ch ^ (rb_ & (CPR - 1))) << 4);
+      ka_off[ks] = (key_a >> 4) * PAGE_BYTES + ra_ * ROWB + ((ch ^ swz_key_pair<HD>(key_a >> 4, ra_)) << 4);
+      kb_off[ks] = (key_b >> 4) * PAGE_BYTES + rb_ * ROWB + ((ch ^ swz_key_pair<HD>(key_b >> 4, rb_)) << 4);
     }
-    v_frag_off = (2 + (grp >> 1)) * PAGE_BYTES + col * 32 + slot_base * 2;
+    v_frag_off = (2 + (grp >> 1)) * PAGE_BYTES + col * 32 + ((slot_base * 2) ^ (swz_value(col) << 4));
   }
   // Running maxima are kept as a lazily updated reference: p = 2^(s - ref) may
   // exceed 1 by up to 2^kRescale before the accumulators are rescaled, which
@@ -1057,7 +1076,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
           }
 #pragma unroll
           for (int q = 0; q < LPP; ++q) {
-            lds_dma16(kp + k_off[q], dst + half * PAGE_BYTES + q * 1024);
+            lds_dma16(kp + k_off[half][q], dst + half * PAGE_BYTES + q * 1024);
             lds_dma16(vp + v_off[q], dst + (2 + half) * PAGE_BYTES + q * 1024);
           }
         }
@@ -1382,7 +1401,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
 template <int DIMS>
 __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int layer_count,
                                                                 int n_wg, int hdr_floats,
-                                                                int nq_pad) {
+                                                                int nq_pad, int waves) {
   constexpr int kBatch = 8, kV = DIMS / 4;
   const int s = blockIdx.x, seg = blockIdx.y;
   const int layer_local = seg / a.Hkv, g = seg % a.Hkv;
@@ -1390,8 +1409,11 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
   const int tid = threadIdx.x;
   const int* hdr = reinterpret_cast<const int*>(a.ws);
   // slice w covers tiles [T w / n_wg, T (w + 1) / n_wg) of the T in the launch
-  // (the launch records T after the slice starts)
-  const int64_t T = hdr[a.S + 1 + n_wg];
+  // (the persistent kernel records T after the slice starts); or, in parts mode
+  // of the per-wavefront kernel (waves > 0), the segment's parts follow the
+  // launch's wavefronts, `waves` of them to a workgroup and its record
+  const int64_t T = hdr[waves > 0 ? 2 * a.S + 2 : a.S + 1 + n_wg];
+  const bool parts = waves > 0 && hdr[2 * a.S + 3] != 0;
   auto bnd = [&](int w) { return static_cast<int>(T * w / n_wg); };
   const SeqInfo si = seq_info(a, s, 1);
   if (!si.ok && seg == 0 && tid == 0 && blockIdx.z == 0) set_status(a.status, CO_ERR_LENGTH);
@@ -1417,13 +1439,23 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
   // uniform over the workgroup: the record base below is a scalar pointer and
   // every load takes a 32-bit lane offset (fewer registers, more workgroups
   // resident per CU)
-  const int w_lo = __builtin_amdgcn_readfirstlane(owner(A));
-  const int w_hi = __builtin_amdgcn_readfirstlane(owner(A + nts - 1));
+  int w_lo, w_hi;
+  if (parts) {
+    const int K1 = hdr[2 * a.S + 1], k0 = seg * K1 + hdr[a.S + 1 + s];
+    const int k1 = seg * K1 + (s + 1 < a.S ? hdr[a.S + 2 + s] : K1);
+    w_lo = k0 / waves;
+    w_hi = (k1 - 1) / waves;
+  } else {
+    w_lo = owner(A);
+    w_hi = owner(A + nts - 1);
+  }
+  w_lo = __builtin_amdgcn_readfirstlane(w_lo);
+  w_hi = __builtin_amdgcn_readfirstlane(w_hi);
   if (w_lo == w_hi) return;            // finished in place
   const int nrec = w_hi - w_lo + 1;
   // with at least as many tiles as slices no slice is empty, so every slot in
   // [w_lo, w_hi] holds a record; otherwise an empty slice left none
-  const bool all_full = T >= n_wg;
+  const bool all_full = parts || T >= n_wg;
   const uint32_t rec = static_cast<uint32_t>(nq_pad) * (hd + a.rec_sums);
   const bool sums = a.rec_sums > 2;    // carry and self sums follow m and l
   // records of consecutive slices of one segment are consecutive slots
@@ -1504,8 +1536,8 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
 // over those keys, and V pages stored [head_dim][16 slots] give the matching
 // A operand with one 16-byte read.  The row maximum is a maximum over 16
 // registers and one exchange between the two halves of the wavefront.  A
-// tile in LDS is [K page 0][K page 1][V page 0][V page 1], K rows with their
-// 16-byte chunks XOR-swizzled by the slot.
+// tile in LDS is [K page 0][K page 1][V page 0][V page 1], rows with their
+// 16-byte chunks XOR-permuted (swz_key_page, swz_value).
 // EXT: two more running sums per query on the same reference, over the carry
 // keys (lu) and the block's own keys (ls), for drafter_block_attention_ext.
 template <int HD, int NQT, bool EXT = false>
@@ -1532,9 +1564,9 @@ struct Tile32 {
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
       const int ch = 2 * k + half;
-      kf_off[k] = (key >> 4) * PAGE_BYTES + kslot * ROWB + ((ch ^ (kslot & (CPR - 1))) << 4);
+      kf_off[k] = (key >> 4) * PAGE_BYTES + kslot * ROWB + ((ch ^ swz_key_page<HD>(kslot)) << 4);
     }
-    vf_off = 2 * PAGE_BYTES + r32 * 32 + half * 16;
+    vf_off = 2 * PAGE_BYTES + r32 * 32 + ((half ^ swz_value(r32)) << 4);
     slot_base = 8 * half;
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
@@ -1889,14 +1921,14 @@ void attn_group_kernel(AttnArgs a, int split_tiles, int n_splits) {
   T.load_q(q_lds + wave * NQP * QLD);
 
   // per-lane source offsets (elements) of the loads of one page: K rows land
-  // XOR-swizzled, V pages are copied as they are
+  // chunks XOR-permuted
   int k_off[LPP], v_off[LPP];
 #pragma unroll
   for (int q = 0; q < LPP; ++q) {
     const int byte = q * 1024 + lane * 16;
     const int r = byte / TT::ROWB, pch = (byte % TT::ROWB) / 16;
-    k_off[q] = r * HD + (pch ^ (r & (TT::CPR - 1))) * 8;
-    v_off[q] = byte / 2;
+    k_off[q] = r * HD + (pch ^ swz_key_page<HD>(r)) * 8;
+    v_off[q] = (byte ^ (swz_value(byte / 32) << 4)) / 2;
   }
   const uint32_t ring_lds = lds_addr(ring);
   // page `phys` of this layer and KV head: base + phys * page_stride elements
@@ -2068,97 +2100,182 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
   }
 }
 
-// ------------------------------------------ bf16 per-wavefront slices path
+// ------------------------------------------------------ bf16 streams path
 //
-// For query tiles too large to stage more than one segment's queries in LDS
-// next to the ring (head_dim 128, 64 query rows), every wavefront takes its
-// own equal slice of the global tile order and walks it alone: no rounds, no
-// barriers, no merging between wavefronts.  Per piece of a segment in the
-// slice, the wavefront loads the queries straight into its MFMA fragments
-// (rotated in registers: at head_dim 128 a lane holds both dims of each
-// rotation pair), streams the piece's tiles through a private two-stage ring
-// and then writes the normalised output (a whole segment) or a record for
-// attn_bf16_combine_kernel (slices are wavefronts: record slot = slice + segment).
-// Tiles of a sequence: its committed pages two by two, then its carry pages
-// two by two.
-constexpr int kWaveRing = 2;     // ring stages per wavefront
-constexpr int kWaveMinTiles = 8; // tiles per slice below which fewer slices are launched
+// For head_dim 128, whose query tiles leave no LDS for the persistent kernel's
+// rounds.  A stream walks its own slice of the tiles: per piece of a segment it
+// loads the queries, then brings the piece's 32-key tiles through a two-stage
+// ring, the next tile's loads issued before the current one is waited for.
+// Tiles of a sequence: its committed pages two by two, then its carry pages two
+// by two.
+//   Up to 32 query rows, a stream is one wavefront and a workgroup holds several
+//   (no barrier in the walk).  With 64 rows it is a workgroup of two wavefronts
+//   that share the ring, one loading the tile's key pages, the other its value
+//   pages, each taking 32 rows: 256 registers apiece, so four such workgroups
+//   keep two wavefronts on every SIMD.  (One wavefront with both row tiles
+//   needed accumulators in AGPRs, and 330 of a tile's 1270 instructions moved
+//   them to VGPRs and back: 2.6 us a tile, as long as its share of the memory
+//   bandwidth.)
+// A second piece costs a stream its queries and first tile again, and the launch
+// waits for the slowest.  So where the segments allow it, a slice is one part of
+// one segment: sequence s is cut into k_s equal parts in every (layer, head),
+// k_s = ceil(tiles / t) with the smallest t whose parts fit the launch.  Streams
+// of one workgroup that hold parts of one segment merge them in LDS: one record
+// per (workgroup, segment), or the finished output where every part is there.
+// Where that t is much above an even share (segments too many or too uneven),
+// slices are equal runs of the global tile order, each piece with a record of
+// its own.  Either way the split is computed on the device from the lengths.
+// Rounds at 32 / 8 heads of 128, one wavefront per slice and a record per piece
+// before, us: 32 contexts of 512-8192 keys 298 -> 278 (this kernel 156 -> 134),
+// with self rows and the carried mass 165 -> 141; 16 contexts of 16-32K keys, 5
+// layers 1564 -> 1544 (5.7 TB/s: the read rate); one of 2048 keys 98 -> 79 (38
+// -> 18); 11 contexts under 1500 keys with 21 query rows, which the persistent
+// kernel took, 71 -> 53.5 (40 -> 23).
+constexpr int kWaveRing = 2;        // ring stages per stream (three stages leave a CU three
+                                    // streams: 285 and 1588 us instead of 278 and 1544 above)
+constexpr int kCuStreams = 4;       // streams resident on a CU (34 KiB of LDS each)
+constexpr int kWaveMinTiles = 4;    // tiles per part below which fewer are cut (2, 4, 8 tiles: the
+                                    // one context above takes 83, 79, 81 us, its 11 53, 53.5, 59)
+constexpr int kWavePieceTiles = 6;  // cost of a second piece in tiles: the even split's handicap
+                                    // (always cutting parts: the 5 layers take 1652 us, not 1544)
+constexpr int kWavePartSeqs = 64;   // sequences (one per lane) up to which segments are cut in parts
 
-// wavefronts per workgroup: one per SIMD at head_dim 128 (registers), two at 64
-constexpr int wave_waves(int hd) { return hd == 128 ? 4 : 8; }
+// Wavefronts per stream and streams per workgroup, by query tiles of 32 rows.
+constexpr int stream_waves(int nqt) { return nqt; }
+constexpr int wg_streams(int hd, int nqt) { return nqt == 2 ? 1 : (hd == 128 ? 4 : 8); }
+
+// Header of the workspace (ints): tiles before each sequence [S+1], parts
+// before each sequence [S+1], total tiles, 1 for parts / 0 for the even split.
+constexpr int wave_hdr_ints(int S) { return (2 * (S + 1) + 2 + 63) / 64 * 64; }
 
 template <int HD, int NQT, bool EXT>
-__global__ __launch_bounds__(64 * wave_waves(HD), 1) void attn_wave_kernel(
-    AttnArgs a, int layer_count, int n_slices, int hdr_floats) {
-  // NQT tiles of 32 query rows, each its own Tile32 stepping over the same key
-  // tile (one fragment set live at a time keeps the registers within budget)
+__global__ __launch_bounds__(64 * stream_waves(NQT) * wg_streams(HD, NQT), 2)
+__attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
+    AttnArgs a, int layer_count, int n_slices, int hdr_floats, int rec_rows) {
   using TT = Tile32<HD, 1, EXT>;
-  constexpr int NQP = NQT * 32, NW = wave_waves(HD), NS = kWaveRing, NTHR = 64 * NW;
+  constexpr int QW = stream_waves(NQT), NST = wg_streams(HD, NQT);
+  constexpr int NQP = NQT * 32, NS = kWaveRing, NTHR = 64 * QW * NST;
   constexpr int PAGE_BYTES = TT::PAGE_BYTES, LPP = TT::LPP, TILE_BYTES = TT::TILE_BYTES;
-  constexpr int KK = TT::KK;
-  static_assert(4 * LPP * (NS - 1) < 64, "vmcnt");
-  __shared__ __align__(16) unsigned char ring[NW * NS * TILE_BYTES];
-  __shared__ int tstart[kMaxAttnSeqs + 1];
-  __shared__ int ctx_l[kMaxAttnSeqs], carry_l[kMaxAttnSeqs];
-  __shared__ int part[NTHR];
+  constexpr int KK = TT::KK, NSUM = EXT ? 4 : 2, CH = HD / 4;   // CH: 16-byte chunks per output row
+  constexpr int TL = 4 * LPP / QW;                              // loads per wavefront and tile
+  static_assert(TL * (NS - 1) < 64, "vmcnt");
+  static_assert(NQP * HD * 4 <= NS * TILE_BYTES, "a stream's partial output fits in its ring");
+  static_assert(32 * HD * 2 * QW <= TILE_BYTES, "the queries fit in one slot");
+  __shared__ __align__(16) unsigned char ring[NST * NS * TILE_BYTES];
+  __shared__ float sums[NST * NSUM * NQP];   // a finished piece's m, l (and the extras' sums)
+  __shared__ int run_l[NST];                 // the segment of each stream's part, or -1
   __shared__ double inv_lds[HD / 2];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int stream = wave / QW, qw = wave % QW;
   const int S = a.S, G = a.Hq / a.Hkv, nq = a.B * G;
+  const int w = blockIdx.x * NST + stream, n_segs = layer_count * a.Hkv;
+  int* hdr = reinterpret_cast<int*>(a.ws);
   if (tid < HD / 2) inv_lds[tid] = a.rope_inv[tid] * kInv2Pi;
 
-  // ---- tiles per sequence and their prefix (the same in every workgroup)
-  constexpr int SPT = (kMaxAttnSeqs + NTHR - 1) / NTHR;   // sequences per thread
-  int nts[SPT];
-  int sum = 0;
+  // tiles of sequence s (its length errors reported once)
+  auto seq_tiles = [&](int s, int& ctx, int& carry) {
+    const SeqInfo si = seq_info(a, s, 1);
+    ctx = si.ok ? si.ctx : 0;
+    carry = si.ok ? si.carry : 0;
+    if (!si.ok && blockIdx.x == 0) set_status(a.status, CO_ERR_LENGTH);
+    const int n = ((ctx + kPage - 1) / kPage + 1) / 2 + ((carry + kPage - 1) / kPage + 1) / 2;
+    return (EXT && a.k_self && si.ok && n == 0) ? 1 : n;   // its self keys follow the tile
+  };
+  auto scan64 = [&](int v) {   // inclusive sum over the lanes
 #pragma unroll
-  for (int i = 0; i < SPT; ++i) {
-    const int s = tid * SPT + i;
-    nts[i] = 0;
-    if (s < S) {
-      const SeqInfo si = seq_info(a, s, 1);
-      const int ctx = si.ok ? si.ctx : 0, carry = si.ok ? si.carry : 0;
-      if (!si.ok && blockIdx.x == 0) set_status(a.status, CO_ERR_LENGTH);
-      ctx_l[s] = ctx;
-      carry_l[s] = carry;
-      const int npc = (ctx + kPage - 1) / kPage, ncp = (carry + kPage - 1) / kPage;
-      nts[i] = (npc + 1) / 2 + (ncp + 1) / 2;
-      if (EXT && a.k_self && si.ok && nts[i] == 0) nts[i] = 1;   // its self keys follow the tile
+    for (int off = 1; off < 64; off <<= 1) {
+      const int u = __shfl_up(v, off);
+      if (lane >= off) v += u;
     }
-    sum += nts[i];
+    return v;
+  };
+
+  // ---- the split (the same in every wavefront, in registers): lane l holds
+  // sequences l * per .. + per - 1, a single one (n_l tiles) where per is 1
+  const int per = (S + 63) / 64;
+  int n_l = 0, ctx_v = 0, carry_v = 0;
+  for (int i = 0; i < per; ++i) {
+    const int s = lane * per + i;
+    if (s < S) n_l += seq_tiles(s, ctx_v, carry_v);
   }
-  part[tid] = sum;
-  __syncthreads();
-  for (int off = 1; off < NTHR; off <<= 1) {   // inclusive scan of the per-thread sums
-    const int v = tid >= off ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
-  }
-  {
-    int x = part[tid] - sum;
+  const int inc_l = scan64(n_l), pre_l = inc_l - n_l;
+  const int T1 = __builtin_amdgcn_readlane(inc_l, 63);
+  int k_l = 0, kpre_l = 0, K1 = 0;
+  bool parts = false;
+  const int ne = __popcll(__ballot(n_l > 0)), budget = n_slices / n_segs;   // parts per segment row
+  if (S <= kWavePartSeqs && ne > 0 && budget >= ne) {
+    int mx = n_l;
 #pragma unroll
-    for (int i = 0; i < SPT; ++i) {
-      const int s = tid * SPT + i;
-      if (s < S) tstart[s] = x;
-      x += nts[i];
+    for (int off = 1; off < 64; off <<= 1) mx = max(mx, __shfl_xor(mx, off));
+    // lane c tries t = lo + c * step; ceil by a reciprocal (any count of at
+    // least one part is a valid cut; every wavefront gets the same)
+    auto cut = [&](int n, int t) {
+      return n > 0 ? max(1, static_cast<int>((static_cast<float>(n + t) - 0.5f) *
+                                             __builtin_amdgcn_rcpf(static_cast<float>(t))))
+                   : 0;
+    };
+    const int lo = max(kWaveMinTiles, (T1 + budget - 1) / budget);
+    const int hi = max(lo, budget > ne ? min(mx, (T1 + budget - ne - 1) / (budget - ne)) : mx);
+    const int step = (hi - lo + 62) / 63, t = lo + lane * step;
+    int sum = 0;
+    for (int s = 0; s < S; ++s) sum += cut(__builtin_amdgcn_readlane(n_l, s), t);
+    const uint64_t fits = __ballot(sum <= budget);
+    if (fits) {
+      const int best = lo + (__ffsll(static_cast<long long>(fits)) - 1) * step;
+      const int64_t even = static_cast<int64_t>(n_segs) * T1 / n_slices;
+      if (best <= max(static_cast<int64_t>(kWaveMinTiles), even + kWavePieceTiles)) {
+        parts = true;
+        k_l = cut(n_l, best);
+        const int kin = scan64(k_l);
+        kpre_l = kin - k_l;
+        K1 = __builtin_amdgcn_readlane(kin, 63);
+      }
     }
-    if (tid == NTHR - 1) tstart[S] = part[NTHR - 1];
   }
-  __syncthreads();
-  const int T1 = tstart[S];
-  const int n_segs = layer_count * a.Hkv;
   const int64_t t_all = static_cast<int64_t>(n_segs) * T1;
-  const int w = blockIdx.x * NW + wave;
-  const int t0 = static_cast<int>(t_all * w / n_slices);
-  const int t1 = static_cast<int>(t_all * (w + 1) / n_slices);
-  int* hdr = reinterpret_cast<int*>(a.ws);
-  if (lane == 0) hdr[S + 1 + w] = t0;
-  if (w == 0) {
-    for (int s = lane; s <= S; s += 64) hdr[s] = tstart[s];
-    if (lane == 0) hdr[S + 1 + n_slices] = static_cast<int>(t_all);
+  if (w == 0 && qw == 0) {
+    int x = pre_l;
+    for (int i = 0; i < per; ++i) {
+      const int s = lane * per + i;
+      if (s < S) {
+        int c, u;
+        hdr[s] = x;
+        x += seq_tiles(s, c, u);
+      }
+    }
+    if (per == 1 && lane < S) hdr[S + 1 + lane] = kpre_l;
+    if (lane == 0) {
+      hdr[S] = T1;
+      hdr[2 * S + 1] = K1;
+      hdr[2 * S + 2] = static_cast<int>(t_all);
+      hdr[2 * S + 3] = parts ? 1 : 0;
+    }
   }
+  // the sequence that holds tile `local` of a segment row, its first and last
+  // tile (exclusive) and its lengths
+  auto locate = [&](int local, int& s, int& ts, int& te, int& ctx, int& carry) {
+    const int L = 63 - __builtin_clzll(__ballot(n_l > 0 && pre_l <= local));
+    if (per == 1) {
+      s = L;
+      ts = __builtin_amdgcn_readlane(pre_l, L);
+      te = ts + __builtin_amdgcn_readlane(n_l, L);
+      ctx = __builtin_amdgcn_readlane(ctx_v, L);
+      carry = __builtin_amdgcn_readlane(carry_v, L);
+      return;
+    }
+    int n = 0, c = 0, u = 0;   // lane L's sequences, one per lane (at most 32)
+    if (lane < per && L * per + lane < S) n = seq_tiles(L * per + lane, c, u);
+    const int end = __builtin_amdgcn_readlane(pre_l, L) + scan64(n), beg = end - n;
+    const int i = 63 - __builtin_clzll(__ballot(n > 0 && beg <= local));
+    s = L * per + i;
+    ts = __builtin_amdgcn_readlane(beg, i);
+    te = __builtin_amdgcn_readlane(end, i);
+    ctx = __builtin_amdgcn_readlane(c, i);
+    carry = __builtin_amdgcn_readlane(u, i);
+  };
+  static_assert(kMaxAttnSeqs <= 64 * 64, "a lane's sequences fit in a wavefront's lanes");
 
   const uint16_t* kc = static_cast<const uint16_t*>(a.k_cache);
   const uint16_t* vc = static_cast<const uint16_t*>(a.v_cache);
@@ -2168,120 +2285,133 @@ __global__ __launch_bounds__(64 * wave_waves(HD), 1) void attn_wave_kernel(
   const bool rotate_q = !(a.flags & CO_Q_PREROTATED);
   const float qscale = rsqrtf(static_cast<float>(HD)) * kLog2e;
   // per-lane source offsets (elements) of the loads of one page: K rows land
-  // XOR-swizzled, V pages are copied as they are
+  // with their chunks XOR-permuted, V pages too
   int k_off[LPP], v_off[LPP];
 #pragma unroll
   for (int q = 0; q < LPP; ++q) {
     const int byte = q * 1024 + lane * 16;
     const int r = byte / TT::ROWB, pch = (byte % TT::ROWB) / 16;
-    k_off[q] = r * HD + (pch ^ (r & (TT::CPR - 1))) * 8;
-    v_off[q] = byte / 2;
+    k_off[q] = r * HD + (pch ^ swz_key_page<HD>(r)) * 8;
+    v_off[q] = (byte ^ (swz_value(byte / 32) << 4)) / 2;
   }
-  const uint32_t my_ring = lds_addr(ring) + wave * NS * TILE_BYTES;
+  unsigned char* my_ring = ring + stream * NS * TILE_BYTES;
+  const uint32_t my_ring_lds = lds_addr(my_ring);
   const int64_t page_stride = static_cast<int64_t>(a.Hkv) * kPage * HD;
   auto load_page = [&](const uint16_t* src, bool is_v, uint32_t dst) {
 #pragma unroll
     for (int q = 0; q < LPP; ++q) lds_dma16_opaque(src + (is_v ? v_off[q] : k_off[q]), dst + q * 1024);
   };
+  auto stream_barrier = [&]() {   // between the wavefronts of a stream
+    if constexpr (QW > 1) stage_barrier();
+  };
+  __syncthreads();   // inv_lds
 
-  TT T[NQT];
-  for (int t = t0; t < t1;) {
-    // ---- the piece of one segment that starts at tile t
-    const int seg = t / T1, local = t - seg * T1;
-    int lo = 0, hi = S;   // the sequence: tstart[s] <= local < tstart[s + 1]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (tstart[mid] <= local) lo = mid; else hi = mid;
-    }
-    const int s = lo;
-    const int j0 = local - tstart[s];
-    const int nts_s = tstart[s + 1] - tstart[s];
-    const int pe = min(t1, seg * T1 + tstart[s + 1]);
-    const int j1 = j0 + (pe - t);
-    const int layer_local = seg / a.Hkv, g = seg % a.Hkv, layer = a.layer_begin + layer_local;
-    const int ctx = ctx_l[s], carry = carry_l[s];
-    const int npc = (ctx + kPage - 1) / kPage, nct = (npc + 1) / 2;
-    const int ncp = (carry + kPage - 1) / kPage;
-
-    // queries of the segment straight into the B fragments, rotated at ctx + i
-    const bool quad = (G & 3) == 0;
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-      T[qt].setup(lane);
-      const int qn = qt * 32 + T[qt].r32;
-      u16x8 raw[KK];
-      const bool live = qn < nq;
-      const int64_t base = live ? out_row(a, layer_local, s, g, qn, G) * HD : 0;
-#pragma unroll
-      for (int k = 0; k < KK; ++k)
-        raw[k] = *reinterpret_cast<const u16x8*>(Q + base + k * 16 + T[qt].half * 8);
-      const int pos = ctx + qn / G;
-#pragma unroll
-      for (int k = 0; k < KK / 2; ++k) {
-        const int i0 = k * 16 + T[qt].half * 8;   // pair index of element 0 of this chunk
-        // With G a multiple of 4 the four lanes of a quad hold rows of one
-        // position and the same dims: each computes two of the chunk's eight
-        // rotation angles and takes the rest from its neighbours.
-        float c2[2] = {0.f, 0.f}, s2[2] = {0.f, 0.f};
-        if (rotate_q && quad) {
-#pragma unroll
-          for (int u = 0; u < 2; ++u) rope_cos_sin_rev(pos, inv_lds[i0 + 2 * (lane & 3) + u], &c2[u], &s2[u]);
+  // The partials that streams [v0, v1) hold of rows [row0, row1) of segment
+  // (seg, s), merged (log-sum-exp rule): the final output, or the record `rec`.
+  // Thread t of nt takes (query row, four dims) items.
+  auto emit_rows = [&](int t, int nt, int row0, int row1, bool whole, int seg, int s, float* rec,
+                       int v0, int v1) {
+#pragma unroll 1
+    for (int idx = t; idx < (row1 - row0) * CH; idx += nt) {
+      const int qn = row0 + idx / CH, ch = idx % CH;
+      float M = -INFINITY;
+      for (int v = v0; v < v1; ++v) M = fmaxf(M, sums[v * NSUM * NQP + qn]);
+      float den = 0.f, den_u = 0.f, den_s = 0.f;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int v = v0; v < v1; ++v) {
+        const float* x = sums + v * NSUM * NQP + qn;
+        // arguments <= 0: the hardware exp2 is exact enough (and 1 at 0)
+        const float f = x[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[0] - M);
+        den += f * x[NQP];
+        if constexpr (EXT) {
+          den_u += f * x[2 * NQP];
+          den_s += f * x[3 * NQP];
         }
-        float xs[8], ys[8];
+        acc += f * *reinterpret_cast<const f32x4*>(ring + v * NS * TILE_BYTES + qn * (HD * 4) +
+                                                   ((ch ^ (qn & 15)) << 4));
+      }
+      if (whole) {
+        const float inv = den > 0.f ? 1.f / den : 0.f;
+        const int64_t row = out_row(a, seg / a.Hkv, s, seg % a.Hkv, qn, G);
+        u16x4 v;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float x = live ? bf2f(raw[k][e]) : 0.f, y = live ? bf2f(raw[k + KK / 2][e]) : 0.f;
-          if (rotate_q) {
-            float cs, sn;
-            if (quad) {
-              cs = quad_bcast(c2[e & 1], e >> 1);
-              sn = quad_bcast(s2[e & 1], e >> 1);
-            } else {
-              rope_cos_sin_rev(pos, inv_lds[i0 + e], &cs, &sn);
-            }
-            const float x2 = x * cs - y * sn, y2 = y * cs + x * sn;
-            x = x2;
-            y = y2;
+        for (int r = 0; r < 4; ++r) v[r] = f2bf(acc[r] * inv);
+        *reinterpret_cast<u16x4*>(static_cast<uint16_t*>(a.out) + row * HD + 4 * ch) = v;
+        if (ch == 0 && a.lse) a.lse[row] = den > 0.f ? (M + log2f(den)) * kLn2 : -INFINITY;
+        if constexpr (EXT) {   // share of the attention over [C;U] on U
+          const float lcu = den - den_s;
+          if (ch == 0 && a.mass) a.mass[row] = lcu > 0.f ? den_u / lcu : 0.f;
+        }
+      } else {
+        *reinterpret_cast<f32x4*>(rec + qn * HD + 4 * ch) = acc;
+        if (ch == 0) {
+          rec[rec_rows * HD + qn] = M;
+          rec[rec_rows * HD + rec_rows + qn] = den;
+          if constexpr (EXT) {
+            rec[rec_rows * HD + 2 * rec_rows + qn] = den_u;
+            rec[rec_rows * HD + 3 * rec_rows + qn] = den_s;
           }
-          xs[e] = x * qscale;
-          ys[e] = y * qscale;
         }
-        typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-        const u32x4v xp = {cvt_pk_bf16(xs[0], xs[1]), cvt_pk_bf16(xs[2], xs[3]),
-                           cvt_pk_bf16(xs[4], xs[5]), cvt_pk_bf16(xs[6], xs[7])};
-        const u32x4v yp = {cvt_pk_bf16(ys[0], ys[1]), cvt_pk_bf16(ys[2], ys[3]),
-                           cvt_pk_bf16(ys[4], ys[5]), cvt_pk_bf16(ys[6], ys[7])};
-        T[qt].qf[0][k] = __builtin_bit_cast(u16x8, xp);
-        T[qt].qf[0][k + KK / 2] = __builtin_bit_cast(u16x8, yp);
       }
     }
+  };
 
-    // tile j of the sequence: two committed pages, or two carry pages
+  // ---- this stream's slice [t0, t1) of the global tile order: one part of one
+  // segment (none past the last), or an even share, walked piece by piece
+  int t0 = 0, t1 = 0;
+  if (parts) {
+    const int pseg = w / K1, rem = w - pseg * K1;
+    if (pseg < n_segs) {
+      const int ps = 63 - __builtin_clzll(__ballot(k_l > 0 && kpre_l <= rem));
+      const int n_s = __builtin_amdgcn_readlane(n_l, ps), k_s = __builtin_amdgcn_readlane(k_l, ps);
+      const int part = rem - __builtin_amdgcn_readlane(kpre_l, ps);
+      const int first = pseg * T1 + __builtin_amdgcn_readlane(pre_l, ps);
+      t0 = first + static_cast<int>(static_cast<int64_t>(n_s) * part / k_s);
+      t1 = first + static_cast<int>(static_cast<int64_t>(n_s) * (part + 1) / k_s);
+    }
+  } else {
+    t0 = static_cast<int>(t_all * w / n_slices);
+    t1 = static_cast<int>(t_all * (w + 1) / n_slices);
+  }
+  t0 = __builtin_amdgcn_readfirstlane(t0);
+  t1 = __builtin_amdgcn_readfirstlane(t1);
+  int held = -1;   // the segment whose part this stream leaves in LDS
+  TT T;
+  for (int t = t0; t < t1;) {
+    const int seg = t / T1, local = t - seg * T1;
+    int s, ts, te, ctx, carry;
+    locate(local, s, ts, te, ctx, carry);
+    const int pe = min(t1, seg * T1 + te), j0 = local - ts, j1 = j0 + (pe - t);
+    const int layer_local = seg / a.Hkv, g = seg % a.Hkv, layer = a.layer_begin + layer_local;
+    const int npc = (ctx + kPage - 1) / kPage, nct = (npc + 1) / 2;
+    const int ncp = (carry + kPage - 1) / kPage;
     const int64_t head0 = (static_cast<int64_t>(layer) * a.num_pages * a.Hkv + g) * (kPage * HD);
     const int32_t* pt = a.page_table + static_cast<int64_t>(s) * a.max_pages;
+    // tile j of the sequence: two committed pages, or two carry pages; of two
+    // wavefronts the first loads the keys, the second the values
     auto issue = [&](int j, int phys0, int phys1) {
-      const uint32_t dst = my_ring + (j % NS) * TILE_BYTES;
-      const uint16_t *k0, *k1, *v0, *v1;
+      const uint32_t dst = my_ring_lds + (j % NS) * TILE_BYTES;
+      int64_t o0, o1;
       if (j < nct) {
-        k0 = kc + head0 + phys0 * page_stride;
-        v0 = vc + head0 + phys0 * page_stride;
-        k1 = kc + head0 + phys1 * page_stride;
-        v1 = vc + head0 + phys1 * page_stride;
+        o0 = head0 + phys0 * page_stride;
+        o1 = head0 + phys1 * page_stride;
       } else {
         // (clamped: a segment with self keys only has one empty tile)
         const int last = max(ncp - 1, 0);
         const int cp0 = min(2 * (j - nct), last), cp1 = min(cp0 + 1, last);
-        const int64_t r0 = ((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp0) * a.Hkv + g;
-        const int64_t r1 = ((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp1) * a.Hkv + g;
-        k0 = kk + r0 * (kPage * HD);
-        v0 = vk + r0 * (kPage * HD);
-        k1 = kk + r1 * (kPage * HD);
-        v1 = vk + r1 * (kPage * HD);
+        o0 = (((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp0) * a.Hkv + g) * (kPage * HD);
+        o1 = (((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp1) * a.Hkv + g) * (kPage * HD);
       }
-      load_page(k0, false, dst);
-      load_page(k1, false, dst + PAGE_BYTES);
-      load_page(v0, true, dst + 2 * PAGE_BYTES);
-      load_page(v1, true, dst + 3 * PAGE_BYTES);
+      if (QW == 1 || qw == 0) {
+        const uint16_t* kb = j < nct ? kc : kk;
+        load_page(kb + o0, false, dst);
+        load_page(kb + o1, false, dst + PAGE_BYTES);
+      }
+      if (QW == 1 || qw == 1) {
+        const uint16_t* vb = j < nct ? vc : vk;
+        load_page(vb + o0, true, dst + 2 * PAGE_BYTES);
+        load_page(vb + o1, true, dst + 3 * PAGE_BYTES);
+      }
     };
     auto keys = [&](int j, int h) {
       return j < nct ? keys_in(ctx, j, h) : keys_in(carry, j - nct, h);
@@ -2305,74 +2435,210 @@ __global__ __launch_bounds__(64 * wave_waves(HD), 1) void attn_wave_kernel(
         bad = (b0 ? 1 : 0) | (b1 ? 2 : 0);
       }
     };
-    auto tile_ids = [&](int j, int& p0, int& p1, int& b) {   // j uniform, committed
-      if (j >= c0 + 64 || j < c0) fetch_ids(j);
-      p0 = __builtin_amdgcn_readlane(id0, j - c0);
-      p1 = __builtin_amdgcn_readlane(id1, j - c0);
-      b = __builtin_amdgcn_readlane(bad, j - c0);
-    };
-    auto issue_tile = [&](int j, int& b) {
+    auto issue_tile = [&](int j, int& rejected) {
       int p0 = 0, p1 = 0;
-      b = 0;
-      if (j < nct) tile_ids(j, p0, p1, b);
+      rejected = 0;
+      if (j < nct) {   // j uniform
+        if (j >= c0 + 64 || j < c0) fetch_ids(j);
+        p0 = __builtin_amdgcn_readlane(id0, j - c0);
+        p1 = __builtin_amdgcn_readlane(id1, j - c0);
+        rejected = __builtin_amdgcn_readlane(bad, j - c0);
+      }
       issue(j, p0, p1);
     };
 
-    int bcur = 0, bnext = 0;
-    issue_tile(j0, bcur);
+    // This wavefront's 32 query rows land raw in the part of the ring's last slot
+    // that its own loads of a later tile will take, with the first tiles' loads
+    // behind them; they are rotated there at ctx + i and scaled (rows' chunks
+    // XOR-permuted as key rows are), then read into the B fragments.  Rows past
+    // nq repeat the last one; nothing of them is stored.
+    int b[NS] = {};   // rejected pages of the tiles in the ring, b[0] the current one's
+    if (j0 < nct) fetch_ids(j0);
+    constexpr int ROWB = HD * 2, CPR = ROWB / 16, CPP = CPR / 2, QL = 32 * ROWB / 1024;
+    const int row0 = 32 * qw;
+    unsigned char* qs = my_ring + ((j0 + NS - 1) % NS) * TILE_BYTES + qw * (TILE_BYTES / QW);
+    // opaque copy: lane arithmetic of the piece's ends would otherwise be kept
+    // in registers over the whole walk
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    {
+      const int64_t qrow0 = out_row(a, layer_local, s, g, 0, G) * HD;
+#pragma unroll
+      for (int q = 0; q < QL; ++q) {
+        const int r = q * (64 / CPR) + ln / CPR, ch = (ln % CPR) ^ swz_key_page<HD>(r & 15);
+        const int n = min(row0 + r, nq - 1);
+        const int off = ((n / G) * a.Hq + n % G) * HD + ch * 8;
+        lds_dma16_opaque(Q + qrow0 + off, lds_addr(qs) + q * 1024);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NS - 1; ++i)
+      if (j0 + i < j1) issue_tile(j0 + i, b[i]);
+    static_assert(NS == 2, "one tile ahead");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");   // the queries are in
+    // With G a multiple of 4 the four lanes of a quad hold rows of one position
+    // and the same dims: each computes two of a chunk's eight rotation angles and
+    // takes the rest from its neighbours.
+    const bool quad = (G & 3) == 0;
+#pragma unroll 1
+    for (int i = 0; i < 32 * CPP / 64; ++i) {
+      const int r = i * (64 / CPP) + ln / (4 * CPP) * 4 + (ln & 3), c = (ln >> 2) % CPP;
+      const int x16 = swz_key_page<HD>(r & 15), pos = ctx + min(row0 + r, nq - 1) / G;
+      unsigned char* lo_p = qs + r * ROWB + ((c ^ x16) << 4);
+      unsigned char* hi_p = qs + r * ROWB + (((c + CPP) ^ x16) << 4);
+      const u16x8 lo = *reinterpret_cast<const u16x8*>(lo_p), hi = *reinterpret_cast<const u16x8*>(hi_p);
+      float c2[2] = {0.f, 0.f}, s2[2] = {0.f, 0.f};
+      if (rotate_q && quad) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) rope_cos_sin_rev(pos, inv_lds[c * 8 + 2 * (ln & 3) + u], &c2[u], &s2[u]);
+      }
+      float xs[8], ys[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x = bf2f(lo[e]), y = bf2f(hi[e]);
+        if (rotate_q) {
+          float cs, sn;
+          if (quad) {
+            cs = quad_bcast(c2[e & 1], e >> 1);
+            sn = quad_bcast(s2[e & 1], e >> 1);
+          } else {
+            rope_cos_sin_rev(pos, inv_lds[c * 8 + e], &cs, &sn);
+          }
+          const float x2 = x * cs - y * sn, y2 = y * cs + x * sn;
+          x = x2;
+          y = y2;
+        }
+        xs[e] = x * qscale;
+        ys[e] = y * qscale;
+      }
+      typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+      const u32x4v xp = {cvt_pk_bf16(xs[0], xs[1]), cvt_pk_bf16(xs[2], xs[3]),
+                         cvt_pk_bf16(xs[4], xs[5]), cvt_pk_bf16(xs[6], xs[7])};
+      const u32x4v yp = {cvt_pk_bf16(ys[0], ys[1]), cvt_pk_bf16(ys[2], ys[3]),
+                         cvt_pk_bf16(ys[4], ys[5]), cvt_pk_bf16(ys[6], ys[7])};
+      *reinterpret_cast<u32x4v*>(lo_p) = xp;
+      *reinterpret_cast<u32x4v*>(hi_p) = yp;
+    }
+    T.setup(lane);
+#pragma unroll
+    for (int k = 0; k < KK; ++k)
+      T.qf[0][k] = *reinterpret_cast<const u16x8*>(
+          qs + (ln & 31) * ROWB + (((2 * k + (ln >> 5)) ^ swz_key_page<HD>(ln & 15)) << 4));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the second tile lands there
+
     for (int j = j0; j < j1; ++j) {
-      const bool more = j + 1 < j1;
-      if (more) issue_tile(j + 1, bnext);   // into the slot of tile j - 1, consumed
-      if (more) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * LPP) : "memory");
+      // A lone wavefront refills tile j - 1's slot, then waits for tile j; two
+      // wait for their halves of tile j first: the barrier publishes it and tells
+      // that both are done with tile j - 1.
+      const bool more = j + NS - 1 < j1;
+      if (QW == 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
+      const int ahead = min(QW == 1 ? NS - 1 : NS - 2, j1 - 1 - j);   // later tiles in flight
+      if (ahead >= 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      const int n0 = (bcur & 1) ? 0 : keys(j, 0), n1 = (bcur & 2) ? 0 : keys(j, 1);
+      stream_barrier();
+      if (QW > 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
+      const int n0 = (b[0] & 1) ? 0 : keys(j, 0), n1 = (b[0] & 2) ? 0 : keys(j, 1);
       if (n0 + n1 > 0) {
         const int kind = (EXT && j >= nct) ? 1 : 0;   // a tile is committed or carry
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt)
-          T[qt].step(ring + (wave * NS + j % NS) * TILE_BYTES, n0, n1, kind, kind);
+        T.step(my_ring + (j % NS) * TILE_BYTES, n0, n1, kind, kind);
       }
-      bcur = bnext;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // tile j is read
+#pragma unroll
+      for (int i = 0; i + 1 < NS; ++i) b[i] = b[i + 1];
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the ring's last tile is read
+    stream_barrier();   // the ring is free
     if constexpr (EXT) {
       // the segment's end: its self keys, in the slot of its last tile
-      if (a.k_self && j1 == nts_s) {
+      if (a.k_self && j1 == te - ts) {
         // both ring slots are free: raw rows in one, the tile in the other
-        unsigned char* slot = ring + (wave * NS + (j1 - 1) % NS) * TILE_BYTES;
-        const unsigned char* raw = ring + (wave * NS + j1 % NS) * TILE_BYTES;
-        static_assert(NS == 2 && 2 * 32 * HD * 2 <= TILE_BYTES, "self staging");
+        unsigned char* slot = my_ring + ((j1 - 1) % NS) * TILE_BYTES;
+        const unsigned char* raw_rows = my_ring + (j1 % NS) * TILE_BYTES;
+        static_assert(2 * 32 * HD * 2 <= TILE_BYTES, "self staging");
         for (int r0 = 0; r0 < a.B; r0 += 32) {
-          self_rows_raw<HD>(a, s, layer_local, g, r0, lane, lds_addr(raw));
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          self_rows_place<HD>(raw, slot, r0, ctx, lane, inv_lds);
+          if (qw == 0) {
+            self_rows_raw<HD>(a, s, layer_local, g, r0, lane, lds_addr(raw_rows));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            self_rows_place<HD>(raw_rows, slot, r0, ctx, lane, inv_lds);
+          }
+          stream_barrier();
           const int nb = a.B - r0;
-#pragma unroll
-          for (int qt = 0; qt < NQT; ++qt)
-            T[qt].step(slot, min(nb, kPage), max(0, min(nb - kPage, kPage)), 2, 2);
+          T.step(slot, min(nb, kPage), max(0, min(nb - kPage, kPage)), 2, 2);
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next rows land
+          stream_barrier();
         }
       }
     }
 
-    // ---- a whole segment: normalise and write; else a record for the combine
-    float* rec = slot_ptr(a, hdr_floats, w + static_cast<int64_t>(seg) * S + s, NQP);
+    // ---- the piece into the stream's drained ring (rows of HD floats, 16-byte
+    // chunks XOR-permuted by the row)
+    float* my_sums = sums + stream * NSUM * NQP;
+    asm volatile("" : "+v"(ln));
+    {
+      const int qn = row0 + (ln & 31);
 #pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-      if (j0 == 0 && j1 == nts_s)
-        T[qt].write_out(a, layer_local, s, g, qt * 32, nq);
-      else
-        T[qt].write_record(rec, NQP, qt * 32);
+      for (int m = 0; m < HD / 32; ++m)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          f32x4 v;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[c] = T.o[0][m][4 * r4 + c];
+          const int ch = 8 * m + 2 * r4 + (ln >> 5);
+          *reinterpret_cast<f32x4*>(my_ring + qn * (HD * 4) + ((ch ^ (qn & 15)) << 4)) = v;
+        }
+      const float l = T.l_run[0] + __shfl_xor(T.l_run[0], 32);
+      float lu = 0.f, ls = 0.f;
+      if constexpr (EXT) {
+        lu = T.lu_run[0] + __shfl_xor(T.lu_run[0], 32);
+        ls = T.ls_run[0] + __shfl_xor(T.ls_run[0], 32);
+      }
+      if (ln < 32) {
+        my_sums[qn] = T.m_run[0];
+        my_sums[NQP + qn] = l;
+        if constexpr (EXT) {
+          my_sums[2 * NQP + qn] = lu;
+          my_sums[3 * NQP + qn] = ls;
+        }
+      }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes
+    // A whole segment is normalised and written, a part leaves a record (each
+    // wavefront its own rows), or stays there for the merge below.
+    const bool whole = j0 == 0 && j1 == te - ts;
+    if (NST > 1 && parts && !whole) {
+      held = seg * S + s;
+    } else {
+      emit_rows(ln, 64, row0, min(nq, row0 + 32), whole, seg, s,
+                slot_ptr(a, hdr_floats, w + static_cast<int64_t>(seg) * S + s, rec_rows), stream, stream + 1);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the ring refills
+    }
+    stream_barrier();
     t = pe;
+  }
+  if (NST == 1 || !parts) return;   // uniform over the launch
+  if (lane == 0) run_l[stream] = held;
+  __syncthreads();
+  // ---- runs of streams that hold parts of one segment, merged by the whole workgroup
+  for (int v0 = 0; v0 < NST;) {
+    const int sigma = run_l[v0];
+    int v1 = v0 + 1;
+    while (v1 < NST && run_l[v1] == sigma) ++v1;
+    if (sigma >= 0) {
+      const int rs = sigma % S, rseg = sigma / S;
+      const int p0 = blockIdx.x * NST + v0 - (rseg * K1 + __shfl(kpre_l, rs));
+      const bool whole = p0 == 0 && v1 - v0 == __shfl(k_l, rs);   // every part is here
+      emit_rows(tid, NTHR, 0, nq, whole, rseg, rs,
+                slot_ptr(a, hdr_floats, blockIdx.x + static_cast<int64_t>(sigma), rec_rows), v0, v1);
+    }
+    v0 = v1;
   }
 }
 
 }  // namespace
 
 // Whether a launch takes the per-wavefront slices path where the shape allows
-// it: by default at head_dim 128 with 64 query rows (measured faster at every
-// such shape); CO_TUNE_ATTN_WAVE chooses.
+// it: by default at head_dim 128 (11 contexts with 21 query rows 53 us against
+// the persistent kernel's 71, with 64 rows see attn_wave_kernel);
+// CO_TUNE_ATTN_WAVE chooses.
 static bool wave_slices_enabled(int hd) {
   const int64_t v = tuning(CO_TUNE_ATTN_WAVE);
   return v >= 0 ? v != 0 : hd == 128;
@@ -2413,26 +2679,25 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
     const int64_t rows_c = static_cast<int64_t>(L) * num_pages * Hkv;
     const int64_t rows_u = static_cast<int64_t>(L) * S * cp * Hkv;
     p.ok = S <= kMaxAttnSeqs && tiles < INT32_MAX && rows_c < INT32_MAX && rows_u < INT32_MAX;
-    // per-wavefront slices for head_dim 128 with 64 query rows: the workspace
-    // covers either path, so that the choice can change between calls
-    // slices: one per wavefront of every CU, but no more than one per
+    // per-wavefront slices for head_dim 128: the workspace covers either path,
+    // so that the choice can change between calls
+    // slices: one per resident stream of every CU, but no more than one per
     // kWaveMinTiles tiles the page table allows (few tiles in many slices would
     // only multiply the records to combine); the workgroup override sets it
-    const int nw_h = wave_waves(hd);
+    const int nw_h = kCuStreams, wg_st = wg_streams(hd, p.nq_pad <= 32 ? 1 : 2);
     const int64_t cap_tiles = static_cast<int64_t>(L) * Hkv * S * ((max_pages + 1) / 2 + (cp + 1) / 2);
     int n_sl = p.n_wg * nw_h;
     if (!wg_forced) {
-      // 7/8 of the CUs: measured faster than all of them at head_dim 128 (fewer
-      // concurrent page streams, fewer records; 0.70 vs 0.69 of peak at the
-      // 5-layer long chain)
-      n_sl = std::max(1, num_cus * 7 / 8) * nw_h;
+      // on 7/8 of the CUs the 5-layer chain takes 1634 us instead of 1582 and 32
+      // contexts 295 instead of 281 (both before the single barrier per tile)
+      n_sl = std::max(1, num_cus) * nw_h;
       const int64_t by_tiles = (cap_tiles / kWaveMinTiles + nw_h - 1) / nw_h * nw_h;
       n_sl = static_cast<int>(std::max<int64_t>(nw_h, std::min<int64_t>(n_sl, by_tiles)));
     }
-    const bool wave_shape = (hd == 128 && p.nq_pad == 64) ||
-                            (hd == 64 && (p.nq_pad == 32 || p.nq_pad == 64));
+    n_sl = (n_sl + wg_st - 1) / wg_st * wg_st;   // whole workgroups
+    const bool wave_shape = hd == 128 || (p.nq_pad == 32 || p.nq_pad == 64);
     if (wave_shape && n_sl <= kMaxMergeSlices) {
-      const int hdr_w = (S + 1 + n_sl + 1 + 63) / 64 * 64;
+      const int hdr_w = wave_hdr_ints(S);
       const size_t bytes_w =
           (hdr_w + (static_cast<size_t>(n_sl) + static_cast<size_t>(L) * Hkv * S) * rec) * 4;
       if (bytes_w > p.bytes) p.bytes = bytes_w;
@@ -2481,13 +2746,13 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
   // (the grouped-prefix kernel has none: its launches take the other paths)
   const bool ext = a.k_self != nullptr || a.mass != nullptr;
   const int n_wg = p.n_wg, hdr_floats = p.hdr_floats;
-  auto combine = [&]() {
+  auto combine = [&](int rec_rows, int waves) {
     if (wide)
       hipLaunchKernelGGL(attn_bf16_combine_kernel<16>, mgrid, dim3(256), 0, stream, a, layer_count,
-                         n_wg, hdr_floats, p.nq_pad);
+                         n_wg, hdr_floats, rec_rows, waves);
     else
       hipLaunchKernelGGL(attn_bf16_combine_kernel<4>, mgrid, dim3(256), 0, stream, a, layer_count,
-                         n_wg, hdr_floats, p.nq_pad);
+                         n_wg, hdr_floats, rec_rows, waves);
   };
   // grouped kernel: any query count with head_dim 64, up to 32 rows with 128
   const int nq = a.B * (a.Hq / a.Hkv);
@@ -2514,27 +2779,29 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
     return hipGetLastError();
   }
   if (a.dtype == CO_DTYPE_BF16 && p.wave) {
-    const int nw = wave_waves(a.hd);
-    const dim3 wgrid(p.n_wg / nw), wblock(64 * nw);
+    const int nqp = p.nq_pad <= 32 ? 32 : 64, nqt = nqp / 32, nst = wg_streams(a.hd, nqt);
+    const dim3 wgrid(p.n_wg / nst), wblock(64 * stream_waves(nqt) * nst);
 #define CO_WAVE_LAUNCH(HD, NQT)                                                              \
   do {                                                                                       \
     if (ext)                                                                                 \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, true>), wgrid, wblock, 0, stream, a,     \
-                         layer_count, p.n_wg, p.hdr_floats);                                 \
+                         layer_count, p.n_wg, p.hdr_floats, p.nq_pad);                                 \
     else                                                                                     \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, false>), wgrid, wblock, 0, stream, a,    \
-                         layer_count, p.n_wg, p.hdr_floats);                                 \
+                         layer_count, p.n_wg, p.hdr_floats, p.nq_pad);                                 \
   } while (0)
-    if (a.hd == 128)
+    if (a.hd == 128 && nqp == 32)
+      CO_WAVE_LAUNCH(128, 1);
+    else if (a.hd == 128)
       CO_WAVE_LAUNCH(128, 2);
-    else if (p.nq_pad == 32)
+    else if (nqp == 32)
       CO_WAVE_LAUNCH(64, 1);
     else
       CO_WAVE_LAUNCH(64, 2);
 #undef CO_WAVE_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    combine();
+    combine(p.nq_pad, nst);
     return hipGetLastError();
   }
   if (a.dtype == CO_DTYPE_BF16) {
@@ -2569,7 +2836,7 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
 #undef CO_ATTN_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    combine();
+    combine(p.nq_pad, 0);
     return hipGetLastError();
   }
   const dim3 grid(p.n_chunks, a.S, layer_count * a.Hkv);

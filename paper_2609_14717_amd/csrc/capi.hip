@@ -12,7 +12,7 @@
 // cannot allocate.  Every device the library runs on holds its own copy until
 // the process ends; host code reaches it only through the per-device address
 // from hipGetSymbolAddress (the name itself is not a device address here).
-constexpr size_t kScratchBytes = size_t{128} << 20;
+constexpr size_t kScratchBytes = CO_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 using namespace co;

@@ -64,6 +64,18 @@ __device__ __forceinline__ void wait_vm_lgkm_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
+// Workgroup barrier for the staged ring.  Each wavefront has already waited
+// (vmcnt) for its own direct-to-LDS loads of the stage it is about to read, and
+// LDS reads are complete once their values feed the MFMAs, so no memory fence
+// is needed -- a fence here would make every wavefront wait for all the later
+// stages still in flight.  The empty asm keeps the compiler from moving LDS
+// accesses across the barrier.
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Two fp32 values -> packed bf16 pair (round to nearest even, v_cvt_pk_bf16_f32).
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   const __bf16 a = static_cast<__bf16>(lo), b = static_cast<__bf16>(hi);

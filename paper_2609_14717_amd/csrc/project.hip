@@ -59,18 +59,6 @@ __device__ __forceinline__ bool z_row_selected(int z_rows, int32_t dst) {
   return z_rows == 0 || (z_rows == 2) == is_carry_row(dst);
 }
 
-// Workgroup barrier for the staged ring.  Each wavefront has already waited
-// (vmcnt) for its own direct-to-LDS loads of the stage it is about to read, and
-// LDS reads are complete once their values feed the MFMAs, so no memory fence
-// is needed -- a fence here would make every wavefront wait for all the later
-// stages still in flight.  The empty asm keeps the compiler from moving LDS
-// accesses across the barrier.
-__device__ __forceinline__ void stage_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // ------------------------------------------------------------ bf16 MFMA GEMM
 
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool HAS_E>
