@@ -71,3 +71,54 @@ def test_stream_split_edges(c):
     torch.testing.assert_close(mass, mass2, rtol=2e-2, atol=2e-3)
     torch.testing.assert_close(out2.float(), out.float(), rtol=2e-2, atol=2e-2 * float(
         out.float().abs().max()))
+
+
+RAMPS = {"rising": (-300.0, 300.0), "falling": (300.0, -300.0), "low": (-260.0, -250.0),
+         "small": (-2.0, 2.0), "edge": (-9.0, 9.0), "high": (250.0, 260.0)}
+
+
+@pytest.mark.parametrize("hd,Hq,shared", [(64, 2, True), (64, 4, True), (64, 2, False), (128, 2, False),
+                                          (128, 4, False), (128, 2, True)])
+@pytest.mark.parametrize("ramp", list(RAMPS))
+def test_softmax_reference(ramp, hd, Hq, shared):
+    """Scores that rise, fall or stay far from 0 along the keys: the running
+    reference starts at 0 only for a first tile near it and follows the maximum.
+    Against 64 bits on the same bf16 inputs; P and O are rounded to bf16 (2^-8
+    each at most, relative to the largest output of the row)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_14717_amd as co
+    S, B, n = 5, 16, 700
+    print(f"[streams] reference {ramp} hd={hd} Hq={Hq} shared={shared}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(hd + Hq)
+    P = n // 16 + 2
+    pt = torch.arange(P, dtype=torch.int32, device="cuda").repeat(S, 1)
+    dims = co.make_dims(S, B, 64, 64, 1, Hq, 1, hd, P, P, "bf16", 1e4)
+    st = co.alloc_state(dims, pt)
+    lo, hi = RAMPS[ramp]
+    key = torch.zeros(P * 16, hd, device="cuda")
+    key[:, 0] = torch.linspace(lo, hi, P * 16, device="cuda")   # the score, with q = sqrt(hd) e_0
+    val = torch.randn(P * 16, hd, generator=g, device="cuda")
+    key, val = key.to(torch.bfloat16), val.to(torch.bfloat16)
+    st["k_cache"].copy_(key.view(1, P, 1, 16, hd))
+    st["v_cache"].copy_(val.view(1, P, 1, 16, hd).transpose(3, 4))
+    lens = [n, n - 1, 333, 31, 1]
+    st["ctx_len"].copy_(torch.tensor(lens, dtype=torch.int32))
+    q = torch.zeros(1, S, B, Hq, hd, device="cuda", dtype=torch.bfloat16)
+    q[..., 0] = (hd ** 0.5 * torch.linspace(0.5, 1.0, B * Hq, device="cuda")).view(B, Hq).to(torch.bfloat16)
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:-1], device="cuda")
+    ws = torch.zeros(co.workspace_bytes(dims, co.CO_WS_ATTENTION), dtype=torch.uint8, device="cuda")
+    co.drafter_block_attention(dims, 0, 1, q, st, out, lse, co.CO_Q_PREROTATED |
+                               (co.CO_ATTN_SHARED_PREFIX if shared else 0), ws)
+    torch.cuda.synchronize()
+    assert co.carryover_read_status(st) == 0
+    # the kernels scale the queries into log2 units and round them to bf16
+    scale = torch.tensor(hd ** -0.5 * np.log2(np.e), dtype=torch.float32, device="cuda")
+    qs = (q.float() * scale).to(torch.bfloat16).double() * np.log(2.0)
+    for s, m in enumerate(lens):
+        x = qs[0, s].reshape(B * Hq, hd) @ key[:m].double().T
+        ref = torch.softmax(x, -1) @ val[:m].double()
+        got = out[0, s].reshape(B * Hq, hd).double()
+        err = (got - ref).abs().amax(-1) / ref.abs().amax(-1)
+        assert float(err.max()) <= 2 * 2.0 ** -8, (s, float(err.max()))
+        torch.testing.assert_close(lse[0, s].reshape(-1).double(), torch.logsumexp(x, -1), rtol=1e-5, atol=1e-3)
