@@ -88,6 +88,7 @@ __device__ __forceinline__ int64_t out_row(const AttnArgs& a, int layer_local, i
 constexpr int kMaxMergeChunks = 64;
 constexpr int kMaxMergeSlices = 4096;   // workgroups of one persistent launch
 constexpr int kCombineWideSegs = 128;   // segments from which the merge takes 16 dims per thread
+constexpr int kCombineGroupSegs = 48;   // and up to which four wavefronts share an item's records
 constexpr int kAttnWaves64 = 8, kAttnWaves128 = 4;             // wavefronts per workgroup
 constexpr int kAttnRoundTiles64 = 64, kAttnRoundTiles128 = 128; // tiles per wavefront per round
 
@@ -543,9 +544,10 @@ struct SelfRows {
 // (keys [32][HD], then values [32][HD]; rows past B repeat row B - 1, their
 // keys are masked by the caller), then are placed job by job into the slot of
 // the tile layout.  The caller waits for the loads (vmcnt) between the two.
+// `keys` and `values` name the halves this wavefront takes.
 template <int HD>
 __device__ void self_rows_raw(const AttnArgs& a, int s, int layer_local, int g, int t0, int lane,
-                              uint32_t raw) {
+                              uint32_t raw, bool keys, bool values) {
   constexpr int ROWB = HD * 2, LOADS = 32 * ROWB / 1024;   // 1 KiB wavefront loads per half
   const int64_t rs = static_cast<int64_t>(a.Hkv) * HD;
   const int64_t base = ((static_cast<int64_t>(layer_local) * a.S + s) * a.B * a.Hkv + g) * HD;
@@ -555,16 +557,18 @@ __device__ void self_rows_raw(const AttnArgs& a, int s, int layer_local, int g, 
   for (int q = 0; q < LOADS; ++q) {
     const int byte = q * 1024 + lane * 16, r = byte / ROWB, c = (byte % ROWB) / 16;
     const int64_t off = min(t0 + r, a.B - 1) * rs + c * 8;
-    lds_dma16_opaque(ks + off, raw + q * 1024);
-    lds_dma16_opaque(vs + off, raw + (LOADS + q) * 1024);
+    if (keys) lds_dma16_opaque(ks + off, raw + q * 1024);
+    if (values) lds_dma16_opaque(vs + off, raw + (LOADS + q) * 1024);
   }
 }
 
+// (Only the first nb rows: the tile step takes no key and no value of the rest.)
 template <int HD>
-__device__ void self_rows_place(const unsigned char* raw, unsigned char* slot, int t0, int ctx,
-                                int lane, const double* inv_rev) {
+__device__ void self_rows_place(const unsigned char* raw, unsigned char* slot, int t0, int nb, int ctx,
+                                int lane, const double* inv_rev, bool keys, bool values) {
   constexpr int ROWB = HD * 2, CPR = ROWB / 16, PAGE_BYTES = kPage * ROWB;
-  constexpr int KJ = (32 * CPR / 2) / 64, VJ = (32 * CPR) / 64;
+  const int rows = min(nb, 32);
+  const int KJ = keys ? (rows * (CPR / 2) + 63) / 64 : 0, VJ = values ? (rows * CPR + 63) / 64 : 0;
   const unsigned char* rv = raw + 32 * ROWB;
 #pragma unroll 2
   for (int i = 0; i < KJ; ++i) {
@@ -1397,8 +1401,13 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(AttnArgs a, int laye
 // maxima and sums and its DIMS partial dims of up to kBatch records are loaded
 // at once, so a segment costs one round trip after the header loads.  Wide
 // threads (16 dims) suit launches of many segments; with few segments, 4 dims
-// per thread spread each segment over more workgroups.
-template <int DIMS>
+// per thread spread each segment over more workgroups, whose four wavefronts
+// (GROUPS) take every fourth record each: up to 32 records in one round trip,
+// where one after the other a segment spread over the whole chip took 7 to 28
+// (one segment of 4K keys, 32 rows of 64 dims: 114 us -> 64; 5 of 64-209 keys
+// 34 -> 21; 16 31 -> 28.  Past kCombineGroupSegs a segment has few records and
+// four times the workgroups cost more: 74 segments 16.7 -> 18.9).
+template <int DIMS, int GROUPS>
 __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int layer_count,
                                                                 int n_wg, int hdr_floats,
                                                                 int nq_pad, int waves) {
@@ -1407,6 +1416,9 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
   const int layer_local = seg / a.Hkv, g = seg % a.Hkv;
   const int hd = a.hd, G = a.Hq / a.Hkv, nq = a.B * G, qd = hd / DIMS;
   const int tid = threadIdx.x;
+  constexpr int NI = 256 / GROUPS;     // items of a workgroup
+  const int item = tid % NI, grp = tid / NI;
+  __shared__ f32x4 part[GROUPS > 1 ? 2 * (GROUPS - 1) * NI : 1];
   const int* hdr = reinterpret_cast<const int*>(a.ws);
   // slice w covers tiles [T w / n_wg, T (w + 1) / n_wg) of the T in the launch
   // (the persistent kernel records T after the slice starts); or, in parts mode
@@ -1460,21 +1472,24 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
   const bool sums = a.rec_sums > 2;    // carry and self sums follow m and l
   // records of consecutive slices of one segment are consecutive slots
   const float* base = slot_ptr(a, hdr_floats, w_lo + static_cast<int64_t>(seg) * a.S + s, nq_pad);
-  for (int idx = tid + blockIdx.z * 256; idx < nq * qd; idx += 256 * gridDim.z) {
-    const int qn = idx / qd, d = (idx % qd) * DIMS;
+  const int idx = item + blockIdx.z * NI;   // the grid covers every item
+  static_assert(GROUPS == 1 || DIMS == 4, "the groups exchange four dims");
+  if (GROUPS > 1 || idx < nq * qd) {
+    // (items past the last repeat it up to the barrier)
+    const int it = min(idx, nq * qd - 1), qn = it / qd, d = (it % qd) * DIMS;
     const uint32_t pm = static_cast<uint32_t>(nq_pad) * hd + qn;
     const uint32_t po = static_cast<uint32_t>(qn) * hd + d;
     float M = -INFINITY, den = 0.f, den_u = 0.f, den_s = 0.f;
     f32x4 acc[kV];
 #pragma unroll
     for (int j = 0; j < kV; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int r0 = 0; r0 < nrec; r0 += kBatch) {   // usually one batch: one round trip
+    for (int r0 = grp; r0 < nrec; r0 += kBatch * GROUPS) {   // usually one batch: one round trip
       float mv[kBatch], lv[kBatch], luv[kBatch], lsv[kBatch];
       f32x4 ov[kBatch][kV];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        const bool in = r0 + i < nrec;
-        const uint32_t ro = static_cast<uint32_t>(r0 + i) * rec;
+        const bool in = r0 + i * GROUPS < nrec;
+        const uint32_t ro = static_cast<uint32_t>(r0 + i * GROUPS) * rec;
         mv[i] = in ? base[ro + pm] : -INFINITY;
         lv[i] = in ? base[ro + pm + nq_pad] : 0.f;
         luv[i] = (in && sums) ? base[ro + pm + 2 * nq_pad] : 0.f;
@@ -1487,8 +1502,8 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
       float Mb = M;
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        const int w = w_lo + r0 + i;
-        if (!(r0 + i < nrec && (all_full || bnd(w) < bnd(w + 1)))) mv[i] = -INFINITY;
+        const int w = w_lo + r0 + i * GROUPS;
+        if (!(r0 + i * GROUPS < nrec && (all_full || bnd(w) < bnd(w + 1)))) mv[i] = -INFINITY;
         Mb = fmaxf(Mb, mv[i]);
       }
       const float f = (M == -INFINITY) ? 0.f : exp2f(M - Mb);
@@ -1507,6 +1522,35 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
         for (int j = 0; j < kV; ++j) acc[j] += wgt * ov[i][j];
       }
       M = Mb;
+    }
+    if constexpr (GROUPS > 1) {   // the groups' partials into the first group's
+      if (grp > 0) {
+        part[2 * (tid - NI)] = acc[0];
+        part[2 * (tid - NI) + 1] = f32x4{M, den, den_u, den_s};
+      }
+      __syncthreads();
+      if (grp > 0 || idx >= nq * qd) return;
+      f32x4 x[GROUPS - 1];
+      float Mt = M;
+#pragma unroll
+      for (int k = 0; k < GROUPS - 1; ++k) {
+        x[k] = part[2 * (k * NI + item) + 1];
+        Mt = fmaxf(Mt, x[k][0]);
+      }
+      const float f = (M == -INFINITY) ? 0.f : exp2f(M - Mt);
+      den *= f;
+      den_u *= f;
+      den_s *= f;
+      acc[0] *= f;
+#pragma unroll
+      for (int k = 0; k < GROUPS - 1; ++k) {
+        const float wgt = (x[k][0] == -INFINITY) ? 0.f : exp2f(x[k][0] - Mt);
+        den += wgt * x[k][1];
+        den_u += wgt * x[k][2];
+        den_s += wgt * x[k][3];
+        acc[0] += wgt * part[2 * (k * NI + item)];
+      }
+      M = Mt;
     }
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const int64_t row = out_row(a, layer_local, s, g, qn, G);
@@ -1609,18 +1653,11 @@ struct Tile32 {
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
       base[qt] = (m_run[qt] == -INFINITY) ? 0.f : m_run[qt];
-      if (__all(base[qt] == 0.f)) {   // the usual reference: start from the constant 0
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        sc[qt] = mfma32x32x16(kf[0], qf[qt][0], zero);
-      } else {
-        f32x16 c;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) c[r] = -base[qt];
-        sc[qt] = mfma32x32x16(kf[0], qf[qt][0], c);
-      }
+      for (int r = 0; r < 16; ++r) sc[qt][r] = -base[qt];
     }
 #pragma unroll
-    for (int k = 1; k < KK; ++k)
+    for (int k = 0; k < KK; ++k)
 #pragma unroll
       for (int qt = 0; qt < NQT; ++qt) sc[qt] = mfma32x32x16(kf[k], qf[qt][k], sc[qt]);
     if (partial) {
@@ -1662,9 +1699,7 @@ struct Tile32 {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v),
                                                          false, false);
         mx[qt] = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) + base[qt];
-        // (a first maximum within kRescale of 0 takes 0 itself as the reference)
-        const float m_top = m_run[qt] == -INFINITY && fabsf(mx[qt]) <= kRescale ? 0.f : mx[qt];
-        const float m_new = mx[qt] > m_run[qt] + kRescale ? m_top : m_run[qt];
+        const float m_new = mx[qt] > m_run[qt] + kRescale ? mx[qt] : m_run[qt];
         const float alpha = (m_new == m_run[qt]) ? 1.f : exp2f(m_run[qt] - m_new);
         l_run[qt] *= alpha;
         if constexpr (EXT) {
@@ -2128,10 +2163,11 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
 
 // ------------------------------------------------------ bf16 streams path
 //
-// For head_dim 128, whose query tiles leave no LDS for the persistent kernel's
-// rounds.  A stream walks its own slice of the tiles: per piece of a segment it
-// loads the queries, then brings the piece's 32-key tiles through a two-stage
-// ring, the next tile's loads issued before the current one is waited for.
+// For query tiles that leave no LDS for the persistent kernel's rounds, and for
+// head_dim 128 (streams_chosen).  A stream walks its own slice of the tiles: per
+// piece of a segment it loads the queries, then brings the piece's 32-key tiles
+// through a two-stage ring, the next tile's loads issued before the current one
+// is waited for.
 // Tiles of a sequence: its committed pages two by two, then its carry pages two
 // by two.
 //   Up to 32 query rows, a stream is one wavefront and a workgroup holds several
@@ -2159,7 +2195,9 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
 // kernel took, 71 -> 53.5 (40 -> 23).
 constexpr int kWaveRing = 2;        // ring stages per stream (three stages leave a CU three
                                     // streams: 285 and 1588 us instead of 278 and 1544 above)
-constexpr int kCuStreams = 4;       // streams resident on a CU (34 KiB of LDS each)
+constexpr int kCuStreams = 4;       // streams per CU of a launch: as many as fit at head_dim 128 (34
+                                    // KiB of LDS each); at 64, six of two wavefronts would, and are
+                                    // slower (16 contexts of 0.1-32K keys 51.6 us instead of 45.5)
 constexpr int kWaveMinTiles = 4;    // tiles per part below which fewer are cut (2, 4, 8 tiles: the
                                     // one context above takes 83, 79, 81 us, its 11 53, 53.5, 59)
 constexpr int kWavePieceTiles = 6;  // cost of a second piece in tiles: the even split's handicap
@@ -2552,17 +2590,36 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
           qs + (ln & 31) * ROWB + (((2 * k + (ln >> 5)) ^ swz_key_page<HD>(ln & 15)) << 4));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the second tile lands there
 
+    // The segment's end has its self keys after the last tile: their raw rows come
+    // in behind it, in the slot its successor would take, each of two wavefronts
+    // bringing and placing one half (the keys are rotated, the values transposed):
+    // 32 contexts of 512-8192 keys at 32 / 8 heads 141 -> 139 us, one of 17-22K keys
+    // in 5 layers with 64 rows of 64 dims 55 -> 44 (with the grouped merge).
+    const bool self_end = EXT && a.k_self && j1 == te - ts;
+    const bool mine_k = qw == 0, mine_v = qw == QW - 1;
+    unsigned char* raw_rows = my_ring + (j1 % NS) * TILE_BYTES;
+    auto self_issue = [&](int r0) {
+      if constexpr (EXT) {
+        int l = lane;
+        asm volatile("" : "+v"(l));   // (as ln above)
+        self_rows_raw<HD>(a, s, layer_local, g, r0, l, lds_addr(raw_rows), mine_k, mine_v);
+      }
+    };
+    static_assert(2 * 32 * HD * 2 / 1024 == TL * QW, "the self rows take as many loads as a tile");
+
     for (int j = j0; j < j1; ++j) {
       // A lone wavefront refills tile j - 1's slot, then waits for tile j; two
       // wait for their halves of tile j first: the barrier publishes it and tells
       // that both are done with tile j - 1.
       const bool more = j + NS - 1 < j1;
       if (QW == 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
-      const int ahead = min(QW == 1 ? NS - 1 : NS - 2, j1 - 1 - j);   // later tiles in flight
-      if (ahead >= 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");
+      if (QW == 1 && self_end && !more) self_issue(0);
+      const bool ahead = QW == 1 && (more || self_end);   // a later tile (or the self rows) in flight
+      if (ahead) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       stream_barrier();
       if (QW > 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
+      if (QW > 1 && self_end && !more) self_issue(0);
       const int n0 = (b[0] & 1) ? 0 : keys(j, 0), n1 = (b[0] & 2) ? 0 : keys(j, 1);
       if (n0 + n1 > 0) {
         const int kind = (EXT && j >= nct) ? 1 : 0;   // a tile is committed or carry
@@ -2575,19 +2632,17 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     stream_barrier();   // the ring is free
     if constexpr (EXT) {
       // the segment's end: its self keys, in the slot of its last tile
-      if (a.k_self && j1 == te - ts) {
-        // both ring slots are free: raw rows in one, the tile in the other
+      if (self_end) {
         unsigned char* slot = my_ring + ((j1 - 1) % NS) * TILE_BYTES;
-        const unsigned char* raw_rows = my_ring + (j1 % NS) * TILE_BYTES;
         static_assert(2 * 32 * HD * 2 <= TILE_BYTES, "self staging");
         for (int r0 = 0; r0 < a.B; r0 += 32) {
-          if (qw == 0) {
-            self_rows_raw<HD>(a, s, layer_local, g, r0, lane, lds_addr(raw_rows));
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            self_rows_place<HD>(raw_rows, slot, r0, ctx, lane, inv_lds);
-          }
-          stream_barrier();
           const int nb = a.B - r0;
+          if (r0 > 0) self_issue(r0);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          int l = lane;
+          asm volatile("" : "+v"(l));
+          self_rows_place<HD>(raw_rows, slot, r0, nb, ctx, l, inv_lds, mine_k, mine_v);
+          stream_barrier();
           T.step(slot, min(nb, kPage), max(0, min(nb - kPage, kPage)), 2, 2);
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next rows land
           stream_barrier();
@@ -2661,13 +2716,37 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
 
 }  // namespace
 
-// Whether a launch takes the per-wavefront slices path where the shape allows
-// it: by default at head_dim 128 (11 contexts with 21 query rows 53 us against
-// the persistent kernel's 71, with 64 rows see attn_wave_kernel);
-// CO_TUNE_ATTN_WAVE chooses.
-static bool wave_slices_enabled(int hd) {
+// Whether a launch takes the streams path; CO_TUNE_ATTN_WAVE chooses.  By
+// default (us against the persistent kernel's):
+//  - head_dim 128: yes (rounds: 40 segments of 160-400 keys 45 against 52, 15 of
+//    16-32K keys 376 against 527), but with the extras and up to 32 query rows,
+//    where a lone wavefront rotates and places the block's own keys at a
+//    segment's end, not while other segments do not hide that: up to 64 of them
+//    over at most 2048 keys (21 of 73-134 keys 33 against 24, 64 of 145-437 29
+//    against 25; but 20 of 556-3114 29 against 34, 232 of 500 30 against 39), and
+//    up to 256 over at most 512 with 16 rows (216 of 80-135 30 against 23, 140 of
+//    287-337 30.5 against 29; 232 of 456-556 30 against 39).  Up to 16 rows half
+//    a row tile is padding: the largest launches, long past the merges and the
+//    launch itself, stay with the persistent kernel's tiles of 16 (1600 segments
+//    of 1688-2371 keys 405 against 391, 480 of 7-9K 435 against 425; at half of
+//    131072 pages they tie, a quarter of it is 2-9% in favour of streams).
+//  - head_dim 64: above 32 query rows (48 contexts of 100-4000 keys with 64 rows
+//    31 against 60, one of 4000 21 against 43; with 16 rows 880 segments take
+//    128 against 100, 24 short ones 25 against 18).  Of two row tiles up to 48
+//    rows leave half of one to padding, so the shortest contexts, which are all
+//    arithmetic, stay with the persistent kernel's tiles of 16 (48 rows: 54
+//    segments of 38-149 keys 37 against 35; 256 of 141-264 63 against 71).
+constexpr int kSelfMaxSegs = 64, kSelfMaxPages = 128, kPadPages = 131072, kShortPages = 16;
+static bool streams_chosen(int hd, int nq, int64_t segs, int max_pages, bool ext) {
   const int64_t v = tuning(CO_TUNE_ATTN_WAVE);
-  return v >= 0 ? v != 0 : hd == 128;
+  if (v >= 0) return v != 0;
+  if (hd == 128) {
+    if (nq > 32) return true;
+    if (!ext) return nq > 16 || segs * max_pages < kPadPages;
+    return segs > (nq <= 16 && max_pages <= kSelfMaxPages / 4 ? 4 : 1) * kSelfMaxSegs ||
+           max_pages > kSelfMaxPages;
+  }
+  return nq > 48 || (nq > 32 && (ext || max_pages > kShortPages));
 }
 
 AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pages, int num_pages,
@@ -2679,10 +2758,9 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
   const int max_lp = max_pages + cp;
   p.ok = true;
   if (dtype == CO_DTYPE_BF16) {
-    // persistent path: one workgroup on 7/8 of the CUs (as the per-wavefront
-    // slices below: fewer concurrent page streams and records; measured faster
-    // than one on every CU with 32 ragged contexts of 0.5-8K keys at head_dim
-    // 64); a record per (slice, segment) pair and, for large query tiles, a
+    // persistent path: one workgroup on 7/8 of the CUs (fewer concurrent page
+    // streams and records; measured faster than one on every CU with 32 ragged
+    // contexts of 0.5-8K keys at head_dim 64); a record per (slice, segment) pair and, for large query tiles, a
     // parking area per wavefront
     const int nw = hd == 64 ? kAttnWaves64 : kAttnWaves128;
     const int rtm = hd == 64 ? kAttnRoundTiles64 : kAttnRoundTiles128;
@@ -2705,8 +2783,8 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
     const int64_t rows_c = static_cast<int64_t>(L) * num_pages * Hkv;
     const int64_t rows_u = static_cast<int64_t>(L) * S * cp * Hkv;
     p.ok = S <= kMaxAttnSeqs && tiles < INT32_MAX && rows_c < INT32_MAX && rows_u < INT32_MAX;
-    // per-wavefront slices for head_dim 128: the workspace covers either path,
-    // so that the choice can change between calls
+    // streams: the workspace covers either path, so that the choice can change
+    // between calls
     // slices: one per resident stream of every CU, but no more than one per
     // kWaveMinTiles tiles the page table allows (few tiles in many slices would
     // only multiply the records to combine); the workgroup override sets it
@@ -2721,17 +2799,16 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
       n_sl = static_cast<int>(std::max<int64_t>(nw_h, std::min<int64_t>(n_sl, by_tiles)));
     }
     n_sl = (n_sl + wg_st - 1) / wg_st * wg_st;   // whole workgroups
-    const bool wave_shape = hd == 128 || (p.nq_pad == 32 || p.nq_pad == 64);
-    if (wave_shape && n_sl <= kMaxMergeSlices) {
+    if (n_sl <= kMaxMergeSlices) {
       const int hdr_w = wave_hdr_ints(S);
       const size_t bytes_w =
           (hdr_w + (static_cast<size_t>(n_sl) + static_cast<size_t>(L) * Hkv * S) * rec) * 4;
       if (bytes_w > p.bytes) p.bytes = bytes_w;
-      if (wave_slices_enabled(hd)) {
-        p.wave = true;
-        p.n_wg = n_sl;
-        p.hdr_floats = hdr_w;
-      }
+      const int64_t segs = static_cast<int64_t>(L) * Hkv * S;
+      p.n_slices = n_sl;
+      p.hdr_slices = hdr_w;
+      p.streams = streams_chosen(hd, nq, segs, max_pages, false);
+      p.streams_ext = streams_chosen(hd, nq, segs, max_pages, true);
     }
   } else {
     // fp32 path: chunks of pages, one workgroup each, two tiles per wavefront:
@@ -2762,23 +2839,29 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
   if (a.S == 0 || layer_count == 0) return hipSuccess;
   const int nt = p.nq_pad / 16;
   // merge grid: one workgroup per 256 (query row, dims) items of a segment,
-  // 16 dims per item with at least kCombineWideSegs segments, else 4
-  const bool wide = static_cast<int64_t>(a.S) * layer_count * a.Hkv >= kCombineWideSegs;
+  // 16 dims per item with at least kCombineWideSegs segments, else 4; per 64
+  // items with up to kCombineGroupSegs
+  const int64_t n_segs = static_cast<int64_t>(a.S) * layer_count * a.Hkv;
+  const bool wide = n_segs >= kCombineWideSegs, grouped = n_segs <= kCombineGroupSegs;
   const int items = (a.B * (a.Hq / a.Hkv)) * (a.hd / (wide ? 16 : 4));
-  const dim3 mgrid(a.S, layer_count * a.Hkv, (items + 255) / 256);
+  const int wg_items = grouped ? 64 : 256;
+  const dim3 mgrid(a.S, layer_count * a.Hkv, (items + wg_items - 1) / wg_items);
   const int items_f32 = (a.B * (a.Hq / a.Hkv)) * (a.hd / 4);
   const dim3 fgrid(a.S, layer_count * a.Hkv, (items_f32 + 255) / 256);
   // the extras (self segment, carry mass): the same kernels' EXT instantiations
   // (the grouped-prefix kernel has none: its launches take the other paths)
   const bool ext = a.k_self != nullptr || a.mass != nullptr;
   const int n_wg = p.n_wg, hdr_floats = p.hdr_floats;
-  auto combine = [&](int rec_rows, int waves) {
+  auto combine = [&](int slices, int hdr, int rec_rows, int waves) {
     if (wide)
-      hipLaunchKernelGGL(attn_bf16_combine_kernel<16>, mgrid, dim3(256), 0, stream, a, layer_count,
-                         n_wg, hdr_floats, rec_rows, waves);
+      hipLaunchKernelGGL((attn_bf16_combine_kernel<16, 1>), mgrid, dim3(256), 0, stream, a, layer_count,
+                         slices, hdr, rec_rows, waves);
+    else if (grouped)
+      hipLaunchKernelGGL((attn_bf16_combine_kernel<4, 4>), mgrid, dim3(256), 0, stream, a, layer_count,
+                         slices, hdr, rec_rows, waves);
     else
-      hipLaunchKernelGGL(attn_bf16_combine_kernel<4>, mgrid, dim3(256), 0, stream, a, layer_count,
-                         n_wg, hdr_floats, rec_rows, waves);
+      hipLaunchKernelGGL((attn_bf16_combine_kernel<4, 1>), mgrid, dim3(256), 0, stream, a, layer_count,
+                         slices, hdr, rec_rows, waves);
   };
   // grouped kernel: any query count with head_dim 64, up to 32 rows with 128
   const int nq = a.B * (a.Hq / a.Hkv);
@@ -2804,17 +2887,17 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
       hipLaunchKernelGGL(attn_share_merge_kernel<128>, cgrid, dim3(256), 0, stream, a, sp, ns, nqp, kGroupSeqs);
     return hipGetLastError();
   }
-  if (a.dtype == CO_DTYPE_BF16 && p.wave) {
+  if (a.dtype == CO_DTYPE_BF16 && (ext ? p.streams_ext : p.streams)) {
     const int nqp = p.nq_pad <= 32 ? 32 : 64, nqt = nqp / 32, nst = wg_streams(a.hd, nqt);
-    const dim3 wgrid(p.n_wg / nst), wblock(64 * stream_waves(nqt) * nst);
+    const dim3 wgrid(p.n_slices / nst), wblock(64 * stream_waves(nqt) * nst);
 #define CO_WAVE_LAUNCH(HD, NQT)                                                              \
   do {                                                                                       \
     if (ext)                                                                                 \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, true>), wgrid, wblock, 0, stream, a,     \
-                         layer_count, p.n_wg, p.hdr_floats, p.nq_pad);                                 \
+                         layer_count, p.n_slices, p.hdr_slices, p.nq_pad);                   \
     else                                                                                     \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, false>), wgrid, wblock, 0, stream, a,    \
-                         layer_count, p.n_wg, p.hdr_floats, p.nq_pad);                                 \
+                         layer_count, p.n_slices, p.hdr_slices, p.nq_pad);                   \
   } while (0)
     if (a.hd == 128 && nqp == 32)
       CO_WAVE_LAUNCH(128, 1);
@@ -2827,7 +2910,7 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
 #undef CO_WAVE_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    combine(p.nq_pad, nst);
+    combine(p.n_slices, p.hdr_slices, p.nq_pad, nst);
     return hipGetLastError();
   }
   if (a.dtype == CO_DTYPE_BF16) {
@@ -2862,7 +2945,7 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
 #undef CO_ATTN_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    combine(p.nq_pad, 0);
+    combine(n_wg, hdr_floats, p.nq_pad, 0);
     return hipGetLastError();
   }
   const dim3 grid(p.n_chunks, a.S, layer_count * a.Hkv);

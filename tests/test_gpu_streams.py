@@ -1,4 +1,4 @@
-"""GPU parity of the head_dim 128 attention at the edges of its split: parts of
+"""GPU parity of the bf16 attention at the edges of its split and dispatch: parts of
 one segment merged in a workgroup, left as records and whole; the even split
 where segments are too many or too uneven; one sequence per lane (64) and
 several (65 and more); one and two query tiles; empty sequences; and, per case,
@@ -16,7 +16,7 @@ from helpers import OracleRun, compare_round  # noqa: E402
 
 BASE = wl.RAGGED32.replace(Dcat=256, d=128, hd=128, theta=1e6, rounds=3, accept=("geom", 0.25))
 CASES = [
-    # S, B, L, Hq, Hkv, contexts
+    # S, B, L, Hq, Hkv, contexts(, head_dim)
     (1, 16, 1, 8, 2, 2100, 2100),     # 64 rows: parts of 4 tiles, one record each
     (1, 7, 1, 6, 2, 2100, 2100),      # 21 rows: the parts of a workgroup merged
     (2, 1, 1, 1, 1, 1, 130),          # one query row; whole segments
@@ -25,6 +25,23 @@ CASES = [
     (64, 4, 1, 8, 8, 1, 40),          # one sequence per lane
     (65, 4, 1, 8, 8, 1, 40),          # two per lane: the even split
     (130, 16, 1, 4, 1, 1, 300),       # three per lane, 64 rows, more pieces than streams
+    # head_dim 64: more than 32 query rows
+    (7, 16, 2, 8, 2, 1, 900, 64),     # 64 rows
+    (3, 13, 1, 3, 1, 100, 700, 64),   # 39 rows
+    (70, 16, 1, 4, 1, 1, 90, 64),     # two sequences per lane, 64 rows
+    # the persistent kernel, its records merged by one wavefront an item or by four
+    (1, 16, 1, 4, 2, 4000, 4000, 64),  # two segments, over a hundred records each
+    (6, 5, 1, 4, 2, 1, 700, 64),      # 10 rows: items past the last in the last workgroup
+    (12, 3, 1, 4, 4, 1, 300, 64),     # 48 segments, and one more row of them
+    (13, 3, 1, 4, 4, 1, 300, 64),
+    (3, 16, 1, 6, 2, 30, 256, 64),    # 48 rows up to 16 pages, and one page more
+    (3, 16, 1, 6, 2, 30, 270, 64),
+    # head_dim 128 with the extras: up to 64 short segments of 30 rows and more, of
+    # 16 rows also 65 (32 pages) and not (33)
+    (16, 15, 1, 8, 4, 1, 200),
+    (17, 15, 1, 8, 4, 1, 200),
+    (17, 16, 1, 4, 4, 1, 512),
+    (17, 16, 1, 4, 4, 1, 528),
 ]
 
 
@@ -34,8 +51,8 @@ def test_stream_split_edges(c):
         pytest.skip("no GPU")
     import paper_2609_14717_amd as co
     from synth.scenario import Scenario
-    S, B, L, Hq, Hkv, lo, hi = c
-    w = BASE.replace(name="streams", S=S, B=B, L=L, Hq=Hq, Hkv=Hkv, ctx_lo=lo, ctx_hi=hi,
+    S, B, L, Hq, Hkv, lo, hi, hd = c if len(c) == 8 else (*c, 128)
+    w = BASE.replace(name="streams", S=S, B=B, L=L, Hq=Hq, Hkv=Hkv, hd=hd, ctx_lo=lo, ctx_hi=hi,
                      seed=0x5EED40 + S + B)
     print(f"[streams] {c}", flush=True)
     sc, orc = Scenario(w), OracleRun(w)
@@ -59,7 +76,7 @@ def test_stream_split_edges(c):
     torch.testing.assert_close(out[:, keep].float(), before[:, keep].float(), rtol=2e-2, atol=2e-2 * float(
         before.float().abs().max()))
     # the extras: mass and self segment in the call, and as calls of their own
-    mk = lambda: (torch.randn(L, S, B, Hkv, 128, device="cuda") * 0.05).to(torch.bfloat16)  # noqa: E731
+    mk = lambda: (torch.randn(L, S, B, Hkv, hd, device="cuda") * 0.05).to(torch.bfloat16)  # noqa: E731
     k_self, v_self, mass, mass2 = mk(), mk(), torch.empty_like(lse), torch.empty_like(lse)
     co.drafter_carry_mass(sc.dims, 0, L, q, sc.st, lse, mass2)
     co.drafter_self_merge(sc.dims, 0, L, q, k_self, v_self, sc.st, out, lse)
@@ -82,7 +99,7 @@ RAMPS = {"rising": (-300.0, 300.0), "falling": (300.0, -300.0), "low": (-260.0, 
 @pytest.mark.parametrize("ramp", list(RAMPS))
 def test_softmax_reference(ramp, hd, Hq, shared):
     """Scores that rise, fall or stay far from 0 along the keys: the running
-    reference starts at 0 only for a first tile near it and follows the maximum.
+    reference is the first tile's maximum and follows later ones.
     Against 64 bits on the same bf16 inputs; P and O are rounded to bf16 (2^-8
     each at most, relative to the largest output of the row)."""
     if not torch.cuda.is_available():
