@@ -1374,7 +1374,8 @@ PbShared pb_shared(void* ws, int M, int Dcat, int d, int n_kv, int hd, int num_c
   const int64_t tiles = static_cast<int64_t>(n_kv / kPbTile) * ((Dcat + kPbTile - 1) / kPbTile);
   const int64_t units = w.Mp / kPbRowUnit;
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>(num_cus / tiles, units / 4));
-  w.rows_per = static_cast<int>((units + want - 1) / want) * kPbRowUnit;
+  // (at least one step: a batch without rows still has a size)
+  w.rows_per = static_cast<int>(std::max<int64_t>(1, (units + want - 1) / want)) * kPbRowUnit;
   w.splits = (w.Mp + w.rows_per - 1) / w.rows_per;
   auto take = [&](int64_t bytes) {   // ws null: only the size is wanted
     char* q = ws ? static_cast<char*>(ws) + w.bytes : nullptr;

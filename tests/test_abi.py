@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -139,6 +140,32 @@ def test_small_workspace_rejected():
     assert _rc(lambda: co.drafter_block_attention(d, 0, 1, FAKE, _fake_state(), FAKE, None, 0,
                                                   FAKE, stream=0, ws_bytes=need_a - 1)) \
         == co.CO_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(dtype="f32"), dict(Dcat=4096, d=2048, hd=128)],
+                         ids=["bf16", "f32", "wide"])
+def test_empty_batch_has_workspace_sizes_and_succeeds(kw):
+    """num_seqs 0 is a valid batch: every size query answers and every call that
+    takes rows returns without a launch.  In a process of its own, which an
+    arithmetic fault on the host would end."""
+    code = (
+        "import sys; sys.path[:0] = %r\n"
+        "from test_abi import *\n"
+        "from test_abi import _dims, _fake_state, _fake_route, _rc\n"
+        "d = _dims(S=0, **%r)\n"
+        "sizes = [co.workspace_bytes(d, k) for k in range(5)]\n"
+        "W = co.weights(FAKE, FAKE, FAKE)\n"
+        "st, rt = _fake_state(), _fake_route()\n"
+        "assert _rc(lambda: co.carryover_project_kv(d, W, FAKE, rt, st, FAKE, stream=0,\n"
+        "                                           ws_bytes=sizes[0])) == co.CO_OK\n"
+        "if d.dtype == 1:\n"
+        "    assert sizes[4] > 0\n"
+        "    assert _rc(lambda: co.carryover_project_kv_backward(\n"
+        "        d, W, FAKE, rt, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, stream=0,\n"
+        "        ws_bytes=sizes[4])) == co.CO_OK\n"
+    ) % ([ROOT, os.path.dirname(os.path.abspath(__file__))], kw)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-800:])
 
 
 def test_import_range_checked_on_host():
