@@ -1387,7 +1387,8 @@ PbShared pb_shared(void* ws, int M, int Dcat, int d, int n_kv, int hd, int num_c
   w.tpart = reinterpret_cast<float*>(take(w.t_parts * nk * 4));
   w.t = reinterpret_cast<float*>(take(nk * 4));
   w.upart = reinterpret_cast<float*>(take(nk / 64 * d * 4));
-  w.part = reinterpret_cast<float*>(take(w.splits > 1 ? w.splits * nk * Dcat * 4 : 0));
+  // (`want` bounds the splits and, unlike them, never falls as rows are added)
+  w.part = reinterpret_cast<float*>(take(want > 1 ? want * nk * Dcat * 4 : 0));
   w.G = reinterpret_cast<float*>(take(nk * Dcat * 4));
   return w;
 }
@@ -1801,18 +1802,24 @@ hipError_t launch_shared(const ProjBwdArgs& a, int n_kv, hipStream_t stream) {
 
 }  // namespace
 
+// The size covers both paths: a program that sizes its workspace once, for its
+// largest batch, calls with fewer rows, which may take the other path, and the
+// per-row products need several times what the shared one does (2560 -> 1024 ->
+// 1024: 354 MB at 16384 rows, 59 MB for the shared product at 22400).
 size_t proj_bwd_ws_bytes(int M, int Dcat, int d, int n_kv, int hd, int num_cus) {
-  if (pb_use_shared(M, Dcat, d, n_kv)) return pb_shared(nullptr, M, Dcat, d, n_kv, hd, num_cus).bytes;
+  const size_t shared = pb_shared(nullptr, M, Dcat, d, n_kv, hd, num_cus).bytes;
   const int64_t Mp = (M + kRowPad - 1) / kRowPad * kRowPad;
   size_t part = gemm_acc_ws_bytes(d, M, Dcat, num_cus);
   part = std::max(part, gemm_acc_ws_bytes(n_kv, d, static_cast<int>(Mp), num_cus));
   part = std::max(part, gemm_acc_ws_bytes(d, static_cast<int>(Mp), n_kv, num_cus));
   part = std::max(part, gemm_acc_ws_bytes(d, Dcat, static_cast<int>(Mp), num_cus));
-  return static_cast<size_t>(2 * pb_up(d * 4) + pb_up(d * (Mp / 2048 + 1) * 4) +
-                             pb_up(static_cast<int64_t>(kDeParts) * Dcat * 4) +
-                             pb_up(d * Mp * 4) + pb_up(Dcat * Mp * 2) +
-                             2 * pb_up(Mp * n_kv * 2) + 2 * pb_up(d * Mp * 2) +
-                             pb_up(static_cast<int64_t>(d) * n_kv * 2)) + part;
+  const size_t per_row =
+      static_cast<size_t>(2 * pb_up(d * 4) + pb_up(d * (Mp / 2048 + 1) * 4) +
+                          pb_up(static_cast<int64_t>(kDeParts) * Dcat * 4) +
+                          pb_up(d * Mp * 4) + pb_up(Dcat * Mp * 2) +
+                          2 * pb_up(Mp * n_kv * 2) + 2 * pb_up(d * Mp * 2) +
+                          pb_up(static_cast<int64_t>(d) * n_kv * 2)) + part;
+  return std::max(shared, per_row);
 }
 
 hipError_t launch_project_backward(const ProjBwdArgs& a, hipStream_t stream) {

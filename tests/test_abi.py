@@ -281,6 +281,22 @@ def test_projection_backward_arguments_checked_on_host():
         assert _rc(lambda: call(d, variant)) == co.CO_ERR_UNSUPPORTED
 
 
+# Dcat, d, NKV (heads of 64): the projection backward changes its products
+# between these row counts (between the second and the third, but for the last,
+# which takes the shared product throughout), and the sizes of the two differ
+PB_ROWS = [(2560, 1024, 1024, (64, 16384, 22400, 65536)), (1536, 768, 768, (64, 6400, 8192, 65536)),
+           (4096, 1024, 512, (64, 6400, 8192, 65536)), (5120, 1024, 512, (64, 7500, 9000, 65536)),
+           (768, 256, 256, (64, 2048, 4096, 65536))]
+
+
+@pytest.mark.parametrize("Dcat,d,n_kv,rows", PB_ROWS, ids=lambda x: str(x))
+def test_projection_backward_size_of_the_largest_batch_serves_smaller_ones(Dcat, d, n_kv, rows):
+    """A workspace sized once, for the largest batch, is enough for every smaller one."""
+    size = [co.workspace_bytes(_dims(S=r, B=1, Dcat=Dcat, d=d, L=1, Hq=n_kv // 128, Hkv=n_kv // 128),
+                               co.CO_WS_PROJECT_BACKWARD) for r in rows]
+    assert size == sorted(size), size
+
+
 def _round(d, W, q=FAKE, lse=None, wsb=1 << 30, flags=0):
     return co.carryover_round(d, W, FAKE, FAKE, FAKE, q, _fake_state(), _fake_route(), FAKE, lse,
                               flags, FAKE, stream=0, ws_bytes=wsb)
