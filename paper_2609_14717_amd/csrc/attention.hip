@@ -1503,7 +1503,13 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
         const int w = w_lo + r0 + i * GROUPS;
-        if (!(r0 + i * GROUPS < nrec && (all_full || bnd(w) < bnd(w + 1)))) mv[i] = -INFINITY;
+        if (!(r0 + i * GROUPS < nrec && (all_full || bnd(w) < bnd(w + 1)))) {
+          // the slot of an empty slice holds whatever the workspace held
+          mv[i] = -INFINITY;
+          lv[i] = luv[i] = lsv[i] = 0.f;
+#pragma unroll
+          for (int j = 0; j < kV; ++j) ov[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         Mb = fmaxf(Mb, mv[i]);
       }
       const float f = (M == -INFINITY) ? 0.f : exp2f(M - Mb);

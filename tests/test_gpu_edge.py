@@ -292,6 +292,33 @@ def test_kernel_variants(w):
         compare_round(sc, orc, rr, O, LSE, out, lse, sc.rt, orc.seqs, f"{w.name} r{r}")
 
 
+@pytest.mark.parametrize("hd,G,S,lo,hi", [(64, 2, 1, 2000, 2000), (64, 4, 3, 40, 900), (128, 2, 1, 2000, 2000),
+                                          (128, 4, 2, 100, 700)])
+def test_workspace_contents_do_not_matter(hd, G, S, lo, hi):
+    """The workspace is scratch of any contents: the round and the extras on one full
+    of NaN patterns give what they give on one of zeros.  Few tiles over many slices,
+    some of which are empty and leave no record."""
+    Scenario, co = _gpu()
+    w = SHAPES[0].replace(name="scratch", S=S, Hq=2 * G, hd=hd, ctx_lo=lo, ctx_hi=hi, seed=0x5EED2D)
+    print(f"[edge] scratch {hd} {G} {S} {hi}", flush=True)
+    got = []
+    for fill in (0, 255):
+        sc = Scenario(w)
+        sc.ws.fill_(fill)
+        hidden, q, draft, target, _ = sc.round_inputs(0)
+        out, lse = sc.new_output()
+        co.carryover_round(sc.dims, sc.W, hidden, draft, target, q, sc.st, sc.rt, out, lse, 0, sc.ws)
+        k_self, v_self = sc.self_kv(0)
+        out2, lse2, mass = torch.empty_like(out), torch.empty_like(lse), torch.empty_like(lse)
+        ws = torch.full((co.workspace_bytes(sc.dims, co.CO_WS_ATTENTION),), fill, dtype=torch.uint8, device="cuda")
+        co.drafter_block_attention_ext(sc.dims, 0, w.L, q, k_self, v_self, sc.st, out2, lse2, mass, 0, ws)
+        torch.cuda.synchronize()
+        assert co.carryover_read_status(sc.st) == 0
+        got.append((out, lse, out2, lse2, mass))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_empty_batch_is_a_no_op():
     """num_seqs = 0: every call succeeds and launches nothing."""
     _, co = _gpu()
