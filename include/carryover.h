@@ -458,7 +458,9 @@ co_status carryover_read_status(const co_state* state, int32_t* host_out, hipStr
  *   CO_TUNE_GEMM_NO_WIDE            1: never the large-tile projection GEMM
  *   CO_TUNE_PROJECT_FUSED_MIN_ROWS  rows from which the fused small-width
  *                                   projection runs (default 4096)
- *   CO_TUNE_ATTN_WAVE               0/1: bf16 attention by per-wavefront slices
+ *   CO_TUNE_ATTN_WAVE               bf16 attention by streams (1: one or two wavefronts
+ *                                   walk a slice of the keys) or by the persistent
+ *                                   kernel (0)
  *   CO_TUNE_ATTN_WORKGROUPS         bf16 attention workgroups (or slices)
  *   CO_TUNE_ATTN_ROUND_TILES        tiles per wavefront per round, persistent
  *                                   attention kernel

@@ -2175,7 +2175,7 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
 // through a two-stage ring, the next tile's loads issued before the current one
 // is waited for.
 // Tiles of a sequence: its committed pages two by two, then its carry pages two
-// by two.
+// by two, then (drafter_block_attention_ext) the block's own rows as one.
 //   Up to 32 query rows, a stream is one wavefront and a workgroup holds several
 //   (no barrier in the walk).  With 64 rows it is a workgroup of two wavefronts
 //   that share the ring, one loading the tile's key pages, the other its value
@@ -2189,7 +2189,8 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
 // one segment: sequence s is cut into k_s equal parts in every (layer, head),
 // k_s = ceil(tiles / t) with the smallest t whose parts fit the launch.  Streams
 // of one workgroup that hold parts of one segment merge them in LDS: one record
-// per (workgroup, segment), or the finished output where every part is there.
+// per (workgroup, segment), or the finished output where every part is there; a
+// segment has its workgroups to itself while there are enough.
 // Where that t is much above an even share (segments too many or too uneven),
 // slices are equal runs of the global tile order, each piece with a record of
 // its own.  Either way the split is computed on the device from the lengths.
@@ -2198,14 +2199,12 @@ __global__ __launch_bounds__(256) void attn_share_merge_kernel(AttnArgs a, int s
 // with self rows and the carried mass 165 -> 141; 16 contexts of 16-32K keys, 5
 // layers 1564 -> 1544 (5.7 TB/s: the read rate); one of 2048 keys 98 -> 79 (38
 // -> 18); 11 contexts under 1500 keys with 21 query rows, which the persistent
-// kernel took, 71 -> 53.5 (40 -> 23).
+// kernel took, 71 -> 49.
 constexpr int kWaveRing = 2;        // ring stages per stream (three stages leave a CU three
                                     // streams: 285 and 1588 us instead of 278 and 1544 above)
 constexpr int kCuStreams = 4;       // streams per CU of a launch: as many as fit at head_dim 128 (34
                                     // KiB of LDS each); at 64, six of two wavefronts would, and are
                                     // slower (16 contexts of 0.1-32K keys 51.6 us instead of 45.5)
-constexpr int kWaveMinTiles = 4;    // tiles per part below which fewer are cut (2, 4, 8 tiles: the
-                                    // one context above takes 83, 79, 81 us, its 11 53, 53.5, 59)
 constexpr int kWavePieceTiles = 6;  // cost of a second piece in tiles: the even split's handicap
                                     // (always cutting parts: the 5 layers take 1652 us, not 1544)
 constexpr int kWavePartSeqs = 64;   // sequences (one per lane) up to which segments are cut in parts
@@ -2214,6 +2213,15 @@ constexpr int kWavePartSeqs = 64;   // sequences (one per lane) up to which segm
 constexpr int stream_waves(int nqt) { return nqt; }
 constexpr int wg_streams(int hd, int nqt) { return nqt == 2 ? 1 : (hd == 128 ? 4 : 8); }
 
+// Tiles per part below which fewer are cut.  A walk of a few tiles is a chain of
+// latencies, so parts that a workgroup's streams merge in LDS are single tiles
+// (32 segments of 80-135 keys, 32 rows of 128: 21 us, 30 with parts of four; with
+// the extras 22, 35 with the own rows behind parts of four); parts of which each
+// leaves a record are longer (33 rows of 64, 32 segments of 80-135 keys: 17 us, 19
+// with parts of four and 17 with two, which take 19 instead of 16 at 20-60 keys).
+constexpr int wave_min_tiles(int hd, int nqt) { return nqt == 2 ? 3 : (hd == 128 ? 1 : 4); }
+constexpr int kSliceTiles = 4;   // tiles per slice of the even split below which fewer are cut
+
 // Header of the workspace (ints): tiles before each sequence [S+1], parts
 // before each sequence [S+1], total tiles, 1 for parts / 0 for the even split.
 constexpr int wave_hdr_ints(int S) { return (2 * (S + 1) + 2 + 63) / 64 * 64; }
@@ -2221,7 +2229,7 @@ constexpr int wave_hdr_ints(int S) { return (2 * (S + 1) + 2 + 63) / 64 * 64; }
 template <int HD, int NQT, bool EXT>
 __global__ __launch_bounds__(64 * stream_waves(NQT) * wg_streams(HD, NQT), 2)
 __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
-    AttnArgs a, int layer_count, int n_slices, int hdr_floats, int rec_rows) {
+    AttnArgs a, int layer_count, int n_places, int n_slices, int hdr_floats, int rec_rows) {
   using TT = Tile32<HD, 1, EXT>;
   constexpr int QW = stream_waves(NQT), NST = wg_streams(HD, NQT);
   constexpr int NQP = NQT * 32, NS = kWaveRing, NTHR = 64 * QW * NST;
@@ -2251,7 +2259,7 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     carry = si.ok ? si.carry : 0;
     if (!si.ok && blockIdx.x == 0) set_status(a.status, CO_ERR_LENGTH);
     const int n = ((ctx + kPage - 1) / kPage + 1) / 2 + ((carry + kPage - 1) / kPage + 1) / 2;
-    return (EXT && a.k_self && si.ok && n == 0) ? 1 : n;   // its self keys follow the tile
+    return n + (EXT && a.k_self && si.ok ? 1 : 0);   // the block's own rows: the last tile
   };
   auto scan64 = [&](int v) {   // inclusive sum over the lanes
 #pragma unroll
@@ -2273,8 +2281,10 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
   const int inc_l = scan64(n_l), pre_l = inc_l - n_l;
   const int T1 = __builtin_amdgcn_readlane(inc_l, 63);
   int k_l = 0, kpre_l = 0, K1 = 0;
+  // (the block's own rows count as a tile: not split off alone into a record)
+  const int t_min = wave_min_tiles(HD, NQT) + (NST == 1 && EXT && a.k_self ? 1 : 0);
   bool parts = false;
-  const int ne = __popcll(__ballot(n_l > 0)), budget = n_slices / n_segs;   // parts per segment row
+  const int ne = __popcll(__ballot(n_l > 0)), budget = n_places / n_segs;   // parts per segment row
   if (S <= kWavePartSeqs && ne > 0 && budget >= ne) {
     int mx = n_l;
 #pragma unroll
@@ -2286,7 +2296,7 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
                                              __builtin_amdgcn_rcpf(static_cast<float>(t))))
                    : 0;
     };
-    const int lo = max(kWaveMinTiles, (T1 + budget - 1) / budget);
+    const int lo = max(t_min, (T1 + budget - 1) / budget);
     const int hi = max(lo, budget > ne ? min(mx, (T1 + budget - ne - 1) / (budget - ne)) : mx);
     const int step = (hi - lo + 62) / 63, t = lo + lane * step;
     int sum = 0;
@@ -2295,11 +2305,16 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     if (fits) {
       const int best = lo + (__ffsll(static_cast<long long>(fits)) - 1) * step;
       const int64_t even = static_cast<int64_t>(n_segs) * T1 / n_slices;
-      if (best <= max(static_cast<int64_t>(kWaveMinTiles), even + kWavePieceTiles)) {
+      if (best <= max(static_cast<int64_t>(t_min), even + kWavePieceTiles)) {
         parts = true;
         k_l = cut(n_l, best);
-        const int kin = scan64(k_l);
-        kpre_l = kin - k_l;
+        // whole workgroups to a segment where there are enough: the fewest share one
+        int places = (k_l + NST - 1) / NST * NST, kin = scan64(places);
+        if (__builtin_amdgcn_readlane(kin, 63) > budget) {
+          places = k_l;
+          kin = scan64(k_l);
+        }
+        kpre_l = kin - places;
         K1 = __builtin_amdgcn_readlane(kin, 63);
       }
     }
@@ -2434,12 +2449,12 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     if (pseg < n_segs) {
       const int ps = 63 - __builtin_clzll(__ballot(k_l > 0 && kpre_l <= rem));
       const int n_s = __builtin_amdgcn_readlane(n_l, ps), k_s = __builtin_amdgcn_readlane(k_l, ps);
-      const int part = rem - __builtin_amdgcn_readlane(kpre_l, ps);
+      const int part = min(rem - __builtin_amdgcn_readlane(kpre_l, ps), k_s);   // k_s: a place left free
       const int first = pseg * T1 + __builtin_amdgcn_readlane(pre_l, ps);
       t0 = first + static_cast<int>(static_cast<int64_t>(n_s) * part / k_s);
-      t1 = first + static_cast<int>(static_cast<int64_t>(n_s) * (part + 1) / k_s);
+      t1 = part < k_s ? first + static_cast<int>(static_cast<int64_t>(n_s) * (part + 1) / k_s) : t0;
     }
-  } else {
+  } else if (w < n_slices) {
     t0 = static_cast<int>(t_all * w / n_slices);
     t1 = static_cast<int>(t_all * (w + 1) / n_slices);
   }
@@ -2466,9 +2481,7 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
         o0 = head0 + phys0 * page_stride;
         o1 = head0 + phys1 * page_stride;
       } else {
-        // (clamped: a segment with self keys only has one empty tile)
-        const int last = max(ncp - 1, 0);
-        const int cp0 = min(2 * (j - nct), last), cp1 = min(cp0 + 1, last);
+        const int cp0 = 2 * (j - nct), cp1 = min(cp0 + 1, ncp - 1);
         o0 = (((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp0) * a.Hkv + g) * (kPage * HD);
         o1 = (((static_cast<int64_t>(layer) * a.S + s) * a.CP + cp1) * a.Hkv + g) * (kPage * HD);
       }
@@ -2505,9 +2518,29 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
         bad = (b0 ? 1 : 0) | (b1 ? 2 : 0);
       }
     };
+    // The block's own rows are the segment's last tile (drafter_block_attention_ext):
+    // they come in raw, in the slot of that tile, and are placed in the other one
+    // (keys rotated, values transposed), each of two wavefronts bringing and placing
+    // its half.  A tile of their own, so that a part can hold them alone: their
+    // placing then runs beside the other parts' walks instead of behind one.
+    const int own = te - ts - (EXT && a.k_self ? 1 : 0);   // that tile; none: past the last
+    const bool mine_k = qw == 0, mine_v = qw == QW - 1;
+    unsigned char* raw_rows = my_ring + (own % NS) * TILE_BYTES;
+    auto own_issue = [&](int r0) {
+      if constexpr (EXT) {
+        int l = lane;
+        asm volatile("" : "+v"(l));   // (as ln below)
+        self_rows_raw<HD>(a, s, layer_local, g, r0, l, lds_addr(raw_rows), mine_k, mine_v);
+      }
+    };
+    static_assert(2 * 32 * HD * 2 / 1024 == TL * QW, "the own rows take as many loads as a tile");
     auto issue_tile = [&](int j, int& rejected) {
       int p0 = 0, p1 = 0;
       rejected = 0;
+      if (EXT && j == own) {
+        own_issue(0);
+        return;
+      }
       if (j < nct) {   // j uniform
         if (j >= c0 + 64 || j < c0) fetch_ids(j);
         p0 = __builtin_amdgcn_readlane(id0, j - c0);
@@ -2550,9 +2583,11 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     // and the same dims: each computes two of a chunk's eight rotation angles and
     // takes the rest from its neighbours.
     const bool quad = (G & 3) == 0;
+    constexpr int RJ = 64 / CPP;                           // rows of a job
+    const int jobs = (min(nq - row0, 32) + RJ - 1) / RJ;   // none for rows of padding only
 #pragma unroll 1
-    for (int i = 0; i < 32 * CPP / 64; ++i) {
-      const int r = i * (64 / CPP) + ln / (4 * CPP) * 4 + (ln & 3), c = (ln >> 2) % CPP;
+    for (int i = 0; i < jobs; ++i) {
+      const int r = i * RJ + ln / (4 * CPP) * 4 + (ln & 3), c = (ln >> 2) % CPP;
       const int x16 = swz_key_page<HD>(r & 15), pos = ctx + min(row0 + r, nq - 1) / G;
       unsigned char* lo_p = qs + r * ROWB + ((c ^ x16) << 4);
       unsigned char* hi_p = qs + r * ROWB + (((c + CPP) ^ x16) << 4);
@@ -2592,40 +2627,20 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     T.setup(lane);
 #pragma unroll
     for (int k = 0; k < KK; ++k)
-      T.qf[0][k] = *reinterpret_cast<const u16x8*>(
+      T.qf[0][k] = (ln & 31) >= jobs * RJ ? u16x8{} : *reinterpret_cast<const u16x8*>(
           qs + (ln & 31) * ROWB + (((2 * k + (ln >> 5)) ^ swz_key_page<HD>(ln & 15)) << 4));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the second tile lands there
 
-    // The segment's end has its self keys after the last tile: their raw rows come
-    // in behind it, in the slot its successor would take, each of two wavefronts
-    // bringing and placing one half (the keys are rotated, the values transposed):
-    // 32 contexts of 512-8192 keys at 32 / 8 heads 141 -> 139 us, one of 17-22K keys
-    // in 5 layers with 64 rows of 64 dims 55 -> 44 (with the grouped merge).
-    const bool self_end = EXT && a.k_self && j1 == te - ts;
-    const bool mine_k = qw == 0, mine_v = qw == QW - 1;
-    unsigned char* raw_rows = my_ring + (j1 % NS) * TILE_BYTES;
-    auto self_issue = [&](int r0) {
-      if constexpr (EXT) {
-        int l = lane;
-        asm volatile("" : "+v"(l));   // (as ln above)
-        self_rows_raw<HD>(a, s, layer_local, g, r0, l, lds_addr(raw_rows), mine_k, mine_v);
-      }
-    };
-    static_assert(2 * 32 * HD * 2 / 1024 == TL * QW, "the self rows take as many loads as a tile");
-
-    for (int j = j0; j < j1; ++j) {
+    for (int j = j0; j < min(j1, own); ++j) {
       // A lone wavefront refills tile j - 1's slot, then waits for tile j; two
       // wait for their halves of tile j first: the barrier publishes it and tells
       // that both are done with tile j - 1.
       const bool more = j + NS - 1 < j1;
       if (QW == 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
-      if (QW == 1 && self_end && !more) self_issue(0);
-      const bool ahead = QW == 1 && (more || self_end);   // a later tile (or the self rows) in flight
-      if (ahead) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");
+      if (QW == 1 && more) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TL) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       stream_barrier();
       if (QW > 1 && more) issue_tile(j + NS - 1, b[NS - 1]);
-      if (QW > 1 && self_end && !more) self_issue(0);
       const int n0 = (b[0] & 1) ? 0 : keys(j, 0), n1 = (b[0] & 2) ? 0 : keys(j, 1);
       if (n0 + n1 > 0) {
         const int kind = (EXT && j >= nct) ? 1 : 0;   // a tile is committed or carry
@@ -2635,15 +2650,14 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
 #pragma unroll
       for (int i = 0; i + 1 < NS; ++i) b[i] = b[i + 1];
     }
-    stream_barrier();   // the ring is free
+    stream_barrier();   // the other slot is free
     if constexpr (EXT) {
-      // the segment's end: its self keys, in the slot of its last tile
-      if (self_end) {
-        unsigned char* slot = my_ring + ((j1 - 1) % NS) * TILE_BYTES;
+      if (j1 > own) {   // the block's own rows, 32 at a time
+        unsigned char* slot = my_ring + ((own + 1) % NS) * TILE_BYTES;
         static_assert(2 * 32 * HD * 2 <= TILE_BYTES, "self staging");
         for (int r0 = 0; r0 < a.B; r0 += 32) {
           const int nb = a.B - r0;
-          if (r0 > 0) self_issue(r0);
+          if (r0 > 0) own_issue(r0);
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           int l = lane;
           asm volatile("" : "+v"(l));
@@ -2722,36 +2736,31 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
 
 }  // namespace
 
-// Whether a launch takes the streams path; CO_TUNE_ATTN_WAVE chooses.  By
-// default (us against the persistent kernel's):
-//  - head_dim 128: yes (rounds: 40 segments of 160-400 keys 45 against 52, 15 of
-//    16-32K keys 376 against 527), but with the extras and up to 32 query rows,
-//    where a lone wavefront rotates and places the block's own keys at a
-//    segment's end, not while other segments do not hide that: up to 64 of them
-//    over at most 2048 keys (21 of 73-134 keys 33 against 24, 64 of 145-437 29
-//    against 25; but 20 of 556-3114 29 against 34, 232 of 500 30 against 39), and
-//    up to 256 over at most 512 with 16 rows (216 of 80-135 30 against 23, 140 of
-//    287-337 30.5 against 29; 232 of 456-556 30 against 39).  Up to 16 rows half
-//    a row tile is padding: the largest launches, long past the merges and the
-//    launch itself, stay with the persistent kernel's tiles of 16 (1600 segments
-//    of 1688-2371 keys 405 against 391, 480 of 7-9K 435 against 425; at half of
-//    131072 pages they tie, a quarter of it is 2-9% in favour of streams).
-//  - head_dim 64: above 32 query rows (48 contexts of 100-4000 keys with 64 rows
-//    31 against 60, one of 4000 21 against 43; with 16 rows 880 segments take
-//    128 against 100, 24 short ones 25 against 18).  Of two row tiles up to 48
-//    rows leave half of one to padding, so the shortest contexts, which are all
-//    arithmetic, stay with the persistent kernel's tiles of 16 (48 rows: 54
-//    segments of 38-149 keys 37 against 35; 256 of 141-264 63 against 71).
-constexpr int kSelfMaxSegs = 64, kSelfMaxPages = 128, kPadPages = 131072, kShortPages = 16;
+// Whether a launch takes the streams path; CO_TUNE_ATTN_WAVE chooses (0 reaches
+// the persistent kernel's instantiations that the rule below never takes, which
+// the tests compare with the oracle).  The host knows the page table's width and
+// not the lengths, so the rule holds for short contexts in a wide table too.  By
+// default (us of the streams against the persistent kernel's, tables eight times
+// as wide as the contexts):
+//  - head_dim 128: yes (32 segments with 32 rows, 20-60 keys 19 against 30, 2000
+//    26 against 40; with the extras and 16 rows, 32 segments of 80-135 keys 19
+//    against 21, 256 of 2000 56 against 89).  Up to 16 rows half a row tile is
+//    padding: without the extras the largest launches, long past the merges and
+//    the launch itself, stay with the persistent kernel's tiles of 16 (16 rows: 256
+//    segments of 1600-2400 keys 58 against 63, of 3-9K 161 against 154, 1600 of
+//    1600-2400 330 against 311; 128 of 3-9K 84 against 88).
+//  - head_dim 64: above 32 query rows (64 rows: 32 segments of 20-60 keys 16
+//    against 21, 256 of 2000 41 against 70; with 16 rows 880 segments take 128
+//    against 100, 24 short ones 25 against 18).  Of two row tiles up to 48 rows
+//    leave half of one to padding: shorter tables stay with the persistent
+//    kernel's tiles of 16 (48 rows, 32 segments of 100-200 keys 17.7 against
+//    16.5, 256 25 against 29; at their worst, 32 of 50-100 keys in a wide table,
+//    the streams take 19 against 16).
+constexpr int kPadSegs = 256, kPadPages = 131072, kShortPages = 16;
 static bool streams_chosen(int hd, int nq, int64_t segs, int max_pages, bool ext) {
   const int64_t v = tuning(CO_TUNE_ATTN_WAVE);
   if (v >= 0) return v != 0;
-  if (hd == 128) {
-    if (nq > 32) return true;
-    if (!ext) return nq > 16 || segs * max_pages < kPadPages;
-    return segs > (nq <= 16 && max_pages <= kSelfMaxPages / 4 ? 4 : 1) * kSelfMaxSegs ||
-           max_pages > kSelfMaxPages;
-  }
+  if (hd == 128) return nq > 16 || ext || segs < kPadSegs || segs * max_pages < kPadPages;
   return nq > 48 || (nq > 32 && (ext || max_pages > kShortPages));
 }
 
@@ -2791,9 +2800,11 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
     p.ok = S <= kMaxAttnSeqs && tiles < INT32_MAX && rows_c < INT32_MAX && rows_u < INT32_MAX;
     // streams: the workspace covers either path, so that the choice can change
     // between calls
-    // slices: one per resident stream of every CU, but no more than one per
-    // kWaveMinTiles tiles the page table allows (few tiles in many slices would
-    // only multiply the records to combine); the workgroup override sets it
+    // slices of the even split: one per resident stream of every CU, but no more
+    // than one per kSliceTiles tiles the page table allows (few tiles in many slices
+    // would only multiply the records to combine); the workgroup override sets it.
+    // Streams launched: more where a workgroup's merge into one record, so that a
+    // launch of parts leaves no more records than slices would
     const int nw_h = kCuStreams, wg_st = wg_streams(hd, p.nq_pad <= 32 ? 1 : 2);
     const int64_t cap_tiles = static_cast<int64_t>(L) * Hkv * S * ((max_pages + 1) / 2 + (cp + 1) / 2);
     int n_sl = p.n_wg * nw_h;
@@ -2801,17 +2812,19 @@ AttnPlan plan_attention(int S, int B, int L, int Hq, int Hkv, int hd, int max_pa
       // on 7/8 of the CUs the 5-layer chain takes 1634 us instead of 1582 and 32
       // contexts 295 instead of 281 (both before the single barrier per tile)
       n_sl = std::max(1, num_cus) * nw_h;
-      const int64_t by_tiles = (cap_tiles / kWaveMinTiles + nw_h - 1) / nw_h * nw_h;
+      const int64_t by_tiles = (cap_tiles / kSliceTiles + nw_h - 1) / nw_h * nw_h;
       n_sl = static_cast<int>(std::max<int64_t>(nw_h, std::min<int64_t>(n_sl, by_tiles)));
     }
     n_sl = (n_sl + wg_st - 1) / wg_st * wg_st;   // whole workgroups
-    if (n_sl <= kMaxMergeSlices) {
+    const int64_t segs = static_cast<int64_t>(L) * Hkv * S;
+    // (the block's own rows are a tile more per segment)
+    if (n_sl <= kMaxMergeSlices && cap_tiles + segs < INT32_MAX) {
       const int hdr_w = wave_hdr_ints(S);
       const size_t bytes_w =
-          (hdr_w + (static_cast<size_t>(n_sl) + static_cast<size_t>(L) * Hkv * S) * rec) * 4;
+          (hdr_w + (static_cast<size_t>(n_sl) + static_cast<size_t>(segs)) * rec) * 4;
       if (bytes_w > p.bytes) p.bytes = bytes_w;
-      const int64_t segs = static_cast<int64_t>(L) * Hkv * S;
       p.n_slices = n_sl;
+      p.n_places = wg_st == 4 && !wg_forced ? std::min(std::max(1, num_cus) * nw_h, wg_st * n_sl) : n_sl;
       p.hdr_slices = hdr_w;
       p.streams = streams_chosen(hd, nq, segs, max_pages, false);
       p.streams_ext = streams_chosen(hd, nq, segs, max_pages, true);
@@ -2895,15 +2908,15 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
   }
   if (a.dtype == CO_DTYPE_BF16 && (ext ? p.streams_ext : p.streams)) {
     const int nqp = p.nq_pad <= 32 ? 32 : 64, nqt = nqp / 32, nst = wg_streams(a.hd, nqt);
-    const dim3 wgrid(p.n_slices / nst), wblock(64 * stream_waves(nqt) * nst);
+    const dim3 wgrid(p.n_places / nst), wblock(64 * stream_waves(nqt) * nst);
 #define CO_WAVE_LAUNCH(HD, NQT)                                                              \
   do {                                                                                       \
     if (ext)                                                                                 \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, true>), wgrid, wblock, 0, stream, a,     \
-                         layer_count, p.n_slices, p.hdr_slices, p.nq_pad);                   \
+                         layer_count, p.n_places, p.n_slices, p.hdr_slices, p.nq_pad);                   \
     else                                                                                     \
       hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, false>), wgrid, wblock, 0, stream, a,    \
-                         layer_count, p.n_slices, p.hdr_slices, p.nq_pad);                   \
+                         layer_count, p.n_places, p.n_slices, p.hdr_slices, p.nq_pad);                   \
   } while (0)
     if (a.hd == 128 && nqp == 32)
       CO_WAVE_LAUNCH(128, 1);

@@ -103,7 +103,8 @@ struct AttnPlan {
   int n_wg, hdr_floats;        // bf16 persistent path: workgroups, header floats
   int round_tiles;             // bf16 persistent path: tiles per wavefront per round
   int64_t park_off;            // bf16 persistent path: parked partials (workspace floats)
-  int n_slices, hdr_slices;    // bf16 streams path: slices, header floats
+  int n_places;                // bf16 streams path: streams launched
+  int n_slices, hdr_slices;    // its slices in the even split, header floats
   bool streams, streams_ext;   // bf16: the streams path, without and with the extras
   int nq_pad;
   bool ok;                     // false: shapes beyond what one launch can cover

@@ -2,7 +2,8 @@
 one segment merged in a workgroup, left as records and whole; the even split
 where segments are too many or too uneven; one sequence per lane (64) and
 several (65 and more); one and two query tiles; empty sequences; and, per case,
-the extras of drafter_block_attention_ext against the stand-alone calls."""
+the extras of drafter_block_attention_ext against the stand-alone calls; and the
+path that each case takes."""
 import numpy as np
 import pytest
 
@@ -13,49 +14,71 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from helpers import OracleRun, compare_round  # noqa: E402
+from test_gpu_edge import SHAPES  # noqa: E402
 
 BASE = wl.RAGGED32.replace(Dcat=256, d=128, hd=128, theta=1e6, rounds=3, accept=("geom", 0.25))
+STREAMS, PERSISTENT = 1, 0   # as the attn_wave override
 CASES = [
-    # S, B, L, Hq, Hkv, contexts(, head_dim)
-    (1, 16, 1, 8, 2, 2100, 2100),     # 64 rows: parts of 4 tiles, one record each
-    (1, 7, 1, 6, 2, 2100, 2100),      # 21 rows: the parts of a workgroup merged
-    (2, 1, 1, 1, 1, 1, 130),          # one query row; whole segments
-    (3, 16, 2, 2, 1, 33, 600),        # 32 rows exactly, several layers
-    (5, 11, 1, 3, 1, 100, 9000),      # 33 rows: two tiles, the second one row; uneven lengths
-    (64, 4, 1, 8, 8, 1, 40),          # one sequence per lane
-    (65, 4, 1, 8, 8, 1, 40),          # two per lane: the even split
-    (130, 16, 1, 4, 1, 1, 300),       # three per lane, 64 rows, more pieces than streams
+    # S, B, L, Hq, Hkv, contexts, head_dim, page table (0: as wide as the contexts), path
+    (1, 16, 1, 8, 2, 2100, 2100, 128, 0, STREAMS),    # 64 rows: parts of 3 tiles, one record each
+    (1, 7, 1, 6, 2, 2100, 2100, 128, 0, STREAMS),     # 21 rows: the parts of a workgroup merged
+    (2, 1, 1, 1, 1, 1, 130, 128, 0, STREAMS),         # one query row; whole segments
+    (3, 16, 2, 2, 1, 33, 600, 128, 0, STREAMS),       # 32 rows exactly, several layers
+    (5, 11, 1, 3, 1, 100, 9000, 128, 0, STREAMS),     # 33 rows: two tiles, the second one row; uneven lengths
+    (64, 4, 1, 8, 8, 1, 40, 128, 0, STREAMS),         # one sequence per lane
+    (65, 4, 1, 8, 8, 1, 40, 128, 0, STREAMS),         # two per lane: the even split
+    (130, 16, 1, 4, 1, 1, 300, 128, 0, STREAMS),      # three per lane, 64 rows, more pieces than streams
     # head_dim 64: more than 32 query rows
-    (7, 16, 2, 8, 2, 1, 900, 64),     # 64 rows
-    (3, 13, 1, 3, 1, 100, 700, 64),   # 39 rows
-    (70, 16, 1, 4, 1, 1, 90, 64),     # two sequences per lane, 64 rows
+    (7, 16, 2, 8, 2, 1, 900, 64, 0, STREAMS),         # 64 rows
+    (3, 13, 1, 3, 1, 100, 700, 64, 0, STREAMS),       # 39 rows
+    (70, 16, 1, 4, 1, 1, 90, 64, 0, STREAMS),         # two sequences per lane, 64 rows
     # the persistent kernel, its records merged by one wavefront an item or by four
-    (1, 16, 1, 4, 2, 4000, 4000, 64),  # two segments, over a hundred records each
-    (6, 5, 1, 4, 2, 1, 700, 64),      # 10 rows: items past the last in the last workgroup
-    (12, 3, 1, 4, 4, 1, 300, 64),     # 48 segments, and one more row of them
-    (13, 3, 1, 4, 4, 1, 300, 64),
-    (3, 16, 1, 6, 2, 30, 256, 64),    # 48 rows up to 16 pages, and one page more
-    (3, 16, 1, 6, 2, 30, 270, 64),
-    # head_dim 128 with the extras: up to 64 short segments of 30 rows and more, of
-    # 16 rows also 65 (32 pages) and not (33)
-    (16, 15, 1, 8, 4, 1, 200),
-    (17, 15, 1, 8, 4, 1, 200),
-    (17, 16, 1, 4, 4, 1, 512),
-    (17, 16, 1, 4, 4, 1, 528),
+    (1, 16, 1, 4, 2, 4000, 4000, 64, 0, PERSISTENT),  # two segments, over a hundred records each
+    (6, 5, 1, 4, 2, 1, 700, 64, 0, PERSISTENT),       # 10 rows: items past the last in the last workgroup
+    (12, 3, 1, 4, 4, 1, 300, 64, 0, PERSISTENT),      # 48 segments, and one more row of them
+    (13, 3, 1, 4, 4, 1, 300, 64, 0, PERSISTENT),
+    (3, 16, 1, 6, 2, 30, 192, 64, 0, PERSISTENT),     # 48 rows: a table of 16 pages, one of 17,
+    (3, 16, 1, 6, 2, 30, 193, 64, 0, STREAMS),        # and one of 400 over the same contexts
+    (3, 16, 1, 6, 2, 30, 192, 64, 400, STREAMS),
+    (3, 16, 1, 8, 2, 30, 192, 64, 0, STREAMS),        # 64 rows: any table
+    # head_dim 128, up to 16 rows: 255 and 256 segments, tables of 131072 pages in all
+    # and just under it, whatever the contexts
+    (51, 16, 1, 5, 5, 1, 200, 128, 520, STREAMS),
+    (32, 16, 1, 8, 8, 1, 200, 128, 512, PERSISTENT),
+    (32, 16, 1, 8, 8, 1, 200, 128, 511, STREAMS),
+    (32, 9, 1, 16, 8, 1, 200, 128, 512, STREAMS),     # 18 rows: any table
+    # few and short segments in a wide table: whole workgroups to a segment, places
+    # left free in them, segments of one tile, two rows of jobs out of four
+    (4, 16, 1, 8, 8, 1, 16, 128, 300, STREAMS),
+    (4, 15, 1, 16, 8, 20, 60, 128, 300, STREAMS),
+    (17, 15, 1, 8, 4, 80, 140, 128, 300, STREAMS),
+    (3, 16, 1, 2, 1, 33, 600, 128, 300, STREAMS),
 ]
 
 
+def widen(co, sc, pages):
+    """The scenario's sequences in a page table of ``pages`` columns."""
+    w, pt = sc.w, sc.st["page_table"]
+    more = torch.zeros((w.S, pages - pt.shape[1]), dtype=torch.int32, device="cuda")
+    sc.st["page_table"] = torch.cat((pt, more), 1).contiguous()
+    sc.dims = co.make_dims(w.S, w.B, w.Dcat, w.d, w.L, w.Hq, w.Hkv, w.hd, pages, sc.dims.num_pages,
+                           w.dtype, w.theta)
+    sc.ws = torch.zeros(co.workspace_bytes(sc.dims, co.CO_WS_ROUND), dtype=torch.uint8, device="cuda")
+
+
 @pytest.mark.parametrize("c", CASES, ids=lambda c: "-".join(map(str, c)))
-def test_stream_split_edges(c):
+def test_stream_split_edges(c, tune):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2609_14717_amd as co
     from synth.scenario import Scenario
-    S, B, L, Hq, Hkv, lo, hi, hd = c if len(c) == 8 else (*c, 128)
+    S, B, L, Hq, Hkv, lo, hi, hd, pages, path = c
     w = BASE.replace(name="streams", S=S, B=B, L=L, Hq=Hq, Hkv=Hkv, hd=hd, ctx_lo=lo, ctx_hi=hi,
                      seed=0x5EED40 + S + B)
     print(f"[streams] {c}", flush=True)
     sc, orc = Scenario(w), OracleRun(w)
+    if pages:
+        widen(co, sc, pages)
     for r, m in enumerate((None, [0, B] * (S // 2) + [B] * (S % 2))):
         hidden, q, draft, target, m = sc.round_inputs(r, m)
         out, lse = sc.new_output()
@@ -64,6 +87,24 @@ def test_stream_split_edges(c):
         assert co.carryover_read_status(sc.st) == 0
         rr, O, LSE = orc.round(r, m=m)
         compare_round(sc, orc, rr, O, LSE, out, lse, sc.rt, orc.seqs, f"streams {c} r{r}")
+    def taken(wave):
+        """The call's output and the path it took: the streams' header in the workspace
+        is 2 S + 4 words, the persistent kernel's goes on with its slices' starts."""
+        tune("attn_wave", wave)
+        x, z = sc.new_output()
+        ws = torch.full((co.workspace_bytes(sc.dims, co.CO_WS_ATTENTION),), 255, dtype=torch.uint8, device="cuda")
+        co.drafter_block_attention(sc.dims, 0, L, q, sc.st, x, z, 0, ws)
+        word = int(ws[:4 * (2 * S + 5)].view(torch.int32)[2 * S + 4])
+        return x, z, STREAMS if word == -1 else PERSISTENT
+
+    both = {}
+    for wave in (PERSISTENT, STREAMS):
+        x, z, by = both[wave] = taken(wave)
+        assert by == wave
+        torch.testing.assert_close(x.float(), out.float(), rtol=2e-2, atol=2e-2 * float(out.float().abs().max()))
+        torch.testing.assert_close(z, lse, rtol=1e-5, atol=1e-3)
+    x, z, by = taken(-1)
+    assert by == path and torch.equal(x, out) and torch.equal(x, both[path][0]) and torch.equal(z, both[path][1])
     # sequences without keys among the others: O = 0, LSE = -inf
     sc.st["ctx_len"][::3] = 0
     sc.st["carry_len"][::3] = 0
@@ -82,6 +123,46 @@ def test_stream_split_edges(c):
     co.drafter_self_merge(sc.dims, 0, L, q, k_self, v_self, sc.st, out, lse)
     out2, lse2 = torch.empty_like(out), torch.empty_like(lse)
     co.drafter_block_attention_ext(sc.dims, 0, L, q, k_self, v_self, sc.st, out2, lse2, mass, 0, ws)
+    torch.cuda.synchronize()
+    assert co.carryover_read_status(sc.st) == 0
+    torch.testing.assert_close(lse2, lse, rtol=1e-2, atol=1e-2)
+    torch.testing.assert_close(mass, mass2, rtol=2e-2, atol=2e-3)
+    torch.testing.assert_close(out2.float(), out.float(), rtol=2e-2, atol=2e-2 * float(
+        out.float().abs().max()))
+
+
+MORE_SHAPES = [   # what SHAPES leaves to the parity suite: 32 rows at 64, 64 rows at 128
+    SHAPES[0].replace(name="nt2_hd64", Hq=4, seed=0x5EED2B),
+    SHAPES[3].replace(name="nt4_hd128", Hq=8, seed=0x5EED2C),
+]
+
+
+@pytest.mark.parametrize("wave", [PERSISTENT, STREAMS])
+@pytest.mark.parametrize("w", SHAPES + MORE_SHAPES, ids=lambda w: w.name)
+def test_every_instantiation(w, wave, tune):
+    """Every query tile count of both paths, whichever the default takes, against the
+    oracle; its extras (instantiations of their own) against the stand-alone calls."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_14717_amd as co
+    from synth.scenario import Scenario
+    print(f"[streams] {w.name} attn_wave={wave}", flush=True)
+    tune("attn_wave", wave)
+    sc, orc = Scenario(w), OracleRun(w)
+    hidden, q, draft, target, m = sc.round_inputs(0)
+    out, lse = sc.new_output()
+    co.carryover_round(sc.dims, sc.W, hidden, draft, target, q, sc.st, sc.rt, out, lse, 0, sc.ws)
+    torch.cuda.synchronize()
+    assert co.carryover_read_status(sc.st) == 0
+    rr, O, LSE = orc.round(0)
+    compare_round(sc, orc, rr, O, LSE, out, lse, sc.rt, orc.seqs, f"{w.name} {wave}")
+    k_self, v_self = sc.self_kv(0)
+    mass, mass2 = torch.empty_like(lse), torch.empty_like(lse)
+    co.drafter_carry_mass(sc.dims, 0, w.L, q, sc.st, lse, mass2)
+    co.drafter_self_merge(sc.dims, 0, w.L, q, k_self, v_self, sc.st, out, lse)
+    ws = torch.zeros(co.workspace_bytes(sc.dims, co.CO_WS_ATTENTION), dtype=torch.uint8, device="cuda")
+    out2, lse2 = torch.empty_like(out), torch.empty_like(lse)
+    co.drafter_block_attention_ext(sc.dims, 0, w.L, q, k_self, v_self, sc.st, out2, lse2, mass, 0, ws)
     torch.cuda.synchronize()
     assert co.carryover_read_status(sc.st) == 0
     torch.testing.assert_close(lse2, lse, rtol=1e-2, atol=1e-2)
