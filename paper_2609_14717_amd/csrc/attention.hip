@@ -1590,7 +1590,12 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
 // 16-byte chunks XOR-permuted (swz_key_page, swz_value).
 // EXT: two more running sums per query on the same reference, over the carry
 // keys (lu) and the block's own keys (ls), for drafter_block_attention_ext.
-template <int HD, int NQT, bool EXT = false>
+// PLO: the PV products also take what the rounding of P to bf16 left (in bf16 too).
+// A weight of exactly 1 (the tile's largest, under a reference of the tile's own)
+// is rounded by nothing, so a reference kept over several tiles costs accuracy:
+// one over each tile 2.6e-3 from 64 bits, over three or four 2.75e-3, with the
+// remainders 2.3e-3.
+template <int HD, int NQT, bool EXT = false, bool PLO = false>
 struct Tile32 {
   static constexpr int KK = HD / 16, MO = HD / 32;
   static constexpr int ROWB = HD * 2, CPR = ROWB / 16;
@@ -1720,7 +1725,7 @@ struct Tile32 {
         for (int r = 0; r < 16; ++r) sc[qt][r] -= shift;
       }
     }
-    u16x8 pk[NQT][2];
+    u16x8 pk[NQT][2], pl[NQT][2];
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
       float p[16];
@@ -1740,6 +1745,14 @@ struct Tile32 {
         const u32x4v w4 = {cvt_pk_bf16(p[8 * j + 0], p[8 * j + 1]), cvt_pk_bf16(p[8 * j + 2], p[8 * j + 3]),
                            cvt_pk_bf16(p[8 * j + 4], p[8 * j + 5]), cvt_pk_bf16(p[8 * j + 6], p[8 * j + 7])};
         pk[qt][j] = __builtin_bit_cast(u16x8, w4);
+        if constexpr (PLO) {
+          u32x4v l4;
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            l4[k] = cvt_pk_bf16(p[8 * j + 2 * k] - __uint_as_float(w4[k] << 16),
+                                p[8 * j + 2 * k + 1] - __uint_as_float(w4[k] & 0xFFFF0000u));
+          pl[qt][j] = __builtin_bit_cast(u16x8, l4);
+        }
       }
     }
 #pragma unroll
@@ -1747,7 +1760,10 @@ struct Tile32 {
 #pragma unroll
       for (int m = 0; m < MO; ++m)
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) o[qt][m] = mfma32x32x16(vf[m][j], pk[qt][j], o[qt][m]);
+        for (int qt = 0; qt < NQT; ++qt) {
+          if constexpr (PLO) o[qt][m] = mfma32x32x16(vf[m][j], pl[qt][j], o[qt][m]);
+          o[qt][m] = mfma32x32x16(vf[m][j], pk[qt][j], o[qt][m]);
+        }
   }
 
   // query tile qt: normalised output rows (bf16) and LSE; rows >= nq skipped
@@ -2226,11 +2242,11 @@ constexpr int kSliceTiles = 4;   // tiles per slice of the even split below whic
 // before each sequence [S+1], total tiles, 1 for parts / 0 for the even split.
 constexpr int wave_hdr_ints(int S) { return (2 * (S + 1) + 2 + 63) / 64 * 64; }
 
-template <int HD, int NQT, bool EXT>
+template <int HD, int NQT, bool EXT, bool PLO>
 __global__ __launch_bounds__(64 * stream_waves(NQT) * wg_streams(HD, NQT), 2)
 __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     AttnArgs a, int layer_count, int n_places, int n_slices, int hdr_floats, int rec_rows) {
-  using TT = Tile32<HD, 1, EXT>;
+  using TT = Tile32<HD, 1, EXT, PLO>;
   constexpr int QW = stream_waves(NQT), NST = wg_streams(HD, NQT);
   constexpr int NQP = NQT * 32, NS = kWaveRing, NTHR = 64 * QW * NST;
   constexpr int PAGE_BYTES = TT::PAGE_BYTES, LPP = TT::LPP, TILE_BYTES = TT::TILE_BYTES;
@@ -2750,7 +2766,7 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
 //    segments of 1600-2400 keys 58 against 63, of 3-9K 161 against 154, 1600 of
 //    1600-2400 330 against 311; 128 of 3-9K 84 against 88).
 //  - head_dim 64: above 32 query rows (64 rows: 32 segments of 20-60 keys 16
-//    against 21, 256 of 2000 41 against 70; with 16 rows 880 segments take 128
+//    against 21, 256 of 2000 43 against 70; with 16 rows 880 segments take 128
 //    against 100, 24 short ones 25 against 18).  Of two row tiles up to 48 rows
 //    leave half of one to padding: shorter tables stay with the persistent
 //    kernel's tiles of 16 (48 rows, 32 segments of 100-200 keys 17.7 against
@@ -2909,23 +2925,29 @@ hipError_t launch_attention(const AttnArgs& a, const AttnPlan& p, int layer_coun
   if (a.dtype == CO_DTYPE_BF16 && (ext ? p.streams_ext : p.streams)) {
     const int nqp = p.nq_pad <= 32 ? 32 : 64, nqt = nqp / 32, nst = wg_streams(a.hd, nqt);
     const dim3 wgrid(p.n_places / nst), wblock(64 * stream_waves(nqt) * nst);
-#define CO_WAVE_LAUNCH(HD, NQT)                                                              \
+    // The remainders of P where parts of three tiles and more stand in for the
+    // persistent kernel's wavefronts with a tile or two each (2 to 5 % of the call):
+    // not up to 32 rows at 128, whose parts are as short, nor above 48, where that
+    // kernel would spill (64 rows, 32 segments of 2000 keys 78 us against 31).
+#define CO_WAVE_LAUNCH(HD, NQT, PLO)                                                         \
   do {                                                                                       \
     if (ext)                                                                                 \
-      hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, true>), wgrid, wblock, 0, stream, a,     \
+      hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, true, PLO>), wgrid, wblock, 0, stream, a,\
                          layer_count, p.n_places, p.n_slices, p.hdr_slices, p.nq_pad);                   \
     else                                                                                     \
-      hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, false>), wgrid, wblock, 0, stream, a,    \
+      hipLaunchKernelGGL((attn_wave_kernel<HD, NQT, false, PLO>), wgrid, wblock, 0, stream, a,\
                          layer_count, p.n_places, p.n_slices, p.hdr_slices, p.nq_pad);                   \
   } while (0)
     if (a.hd == 128 && nqp == 32)
-      CO_WAVE_LAUNCH(128, 1);
+      CO_WAVE_LAUNCH(128, 1, false);
+    else if (a.hd == 128 && nq <= 48)
+      CO_WAVE_LAUNCH(128, 2, true);
     else if (a.hd == 128)
-      CO_WAVE_LAUNCH(128, 2);
+      CO_WAVE_LAUNCH(128, 2, false);
     else if (nqp == 32)
-      CO_WAVE_LAUNCH(64, 1);
+      CO_WAVE_LAUNCH(64, 1, false);
     else
-      CO_WAVE_LAUNCH(64, 2);
+      CO_WAVE_LAUNCH(64, 2, true);
 #undef CO_WAVE_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
