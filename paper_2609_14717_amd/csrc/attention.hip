@@ -2233,9 +2233,12 @@ constexpr int wg_streams(int hd, int nqt) { return nqt == 2 ? 1 : (hd == 128 ? 4
 // latencies, so parts that a workgroup's streams merge in LDS are single tiles
 // (32 segments of 80-135 keys, 32 rows of 128: 21 us, 30 with parts of four; with
 // the extras 22, 35 with the own rows behind parts of four); parts of which each
-// leaves a record are longer (33 rows of 64, 32 segments of 80-135 keys: 17 us, 19
-// with parts of four and 17 with two, which take 19 instead of 16 at 20-60 keys).
-constexpr int wave_min_tiles(int hd, int nqt) { return nqt == 2 ? 3 : (hd == 128 ? 1 : 4); }
+// leaves a record are of four (8 segments of 8-16K keys, 64 rows of 128: 47 us, 50
+// with parts of three), or of three where no segment of the launch has more than
+// two of those (33 rows of 64, 32 segments of 80-135 keys: 17 us, 19 with parts of
+// four and 17 with two, which take 19 instead of 16 at 20-60 keys).
+constexpr int wave_min_tiles(int hd, int nqt) { return nqt == 1 && hd == 128 ? 1 : 4; }
+constexpr int kShortParts = 3;
 constexpr int kSliceTiles = 4;   // tiles per slice of the even split below which fewer are cut
 
 // Header of the workspace (ints): tiles before each sequence [S+1], parts
@@ -2297,14 +2300,15 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
   const int inc_l = scan64(n_l), pre_l = inc_l - n_l;
   const int T1 = __builtin_amdgcn_readlane(inc_l, 63);
   int k_l = 0, kpre_l = 0, K1 = 0;
-  // (the block's own rows count as a tile: not split off alone into a record)
-  const int t_min = wave_min_tiles(HD, NQT) + (NST == 1 && EXT && a.k_self ? 1 : 0);
   bool parts = false;
   const int ne = __popcll(__ballot(n_l > 0)), budget = n_places / n_segs;   // parts per segment row
   if (S <= kWavePartSeqs && ne > 0 && budget >= ne) {
     int mx = n_l;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) mx = max(mx, __shfl_xor(mx, off));
+    // (with the block's own rows a tile, parts of three would split it off alone)
+    const int t_min = NST == 1 && mx <= 2 * kShortParts && !(EXT && a.k_self)
+                          ? kShortParts : wave_min_tiles(HD, NQT);
     // lane c tries t = lo + c * step; ceil by a reciprocal (any count of at
     // least one part is a valid cut; every wavefront gets the same)
     auto cut = [&](int n, int t) {

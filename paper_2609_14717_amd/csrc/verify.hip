@@ -13,23 +13,22 @@
 //     a correction whose weights are all zero): y is the smallest token whose
 //     running integer sum exceeds floor(word * W / 2^32), W the total weight.
 //
-// One workgroup of 16 wavefronts per sequence (no scratch memory reaches this
-// call, so a row's total cannot be summed across workgroups).  The first
-// wavefront takes the acceptance decisions with one ballot per 64 positions.
-// Then the row of p (and q) is read once: every wavefront sums the weights of
-// its own contiguous sixteenth, and only the sixteenth that holds the draw is
-// read again for the running sums.  The row is bound by what one CU can keep in
-// flight, so a lane has four 16-byte loads of each array outstanding (128 KiB
-// per workgroup).  Integer sums: any order gives the same result.
-// 32 sequences of 128000 tokens: 421 us with one load
-// in flight per thread, 256 threads and two passes, 20 us now.
+// One workgroup of 2 to 16 wavefronts per sequence, by their number and the row's
+// length (no scratch memory reaches this call, so a row's total is not summed
+// across workgroups).  The first wavefront takes the acceptance decisions with one
+// ballot per 64 positions.  Then the row of p (and q) is read once: every wavefront
+// sums the weights of its own contiguous part, and only the part that holds the
+// draw is read again for the running sums.  The row is bound by what one CU can
+// keep in flight, so a lane has four 16-byte loads of each array outstanding (128
+// KiB per workgroup of sixteen).  Integer sums: any order gives the same result.
+// 32 sequences of 128000 tokens: 421 us with one load in flight per thread, 256
+// threads and two passes, 20 us now.
 #include "co_kernels.h"
 
 namespace co {
 
 namespace {
 
-constexpr int kVerifyThreads = 1024, kVerifyWaves = kVerifyThreads / 64;
 constexpr int kVerifyStep = 256;   // tokens of one wavefront load (four per lane)
 constexpr int kVerifyDepth = 4;    // such loads in flight per array
 constexpr int kFindPer = 8;        // tokens per thread and step of the draw's search
@@ -87,8 +86,9 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
 }
 
 // Tokens per wavefront: whole loads, so that only the row's end is ragged.
+template <int NW>
 __device__ __forceinline__ int wave_tokens(int V) {
-  const int64_t unit = static_cast<int64_t>(kVerifyWaves) * kVerifyStep;
+  const int64_t unit = static_cast<int64_t>(NW) * kVerifyStep;
   return static_cast<int>((V + unit - 1) / unit) * kVerifyStep;
 }
 
@@ -129,29 +129,32 @@ __device__ void part_total(const float* p, const float* q, int V, int R, uint64_
   if (lane == 0) red[wave] = s;
 }
 
+template <int NW>
 __device__ uint64_t row_total(const float* p, const float* q, int V, int R, uint64_t* red) {
   __syncthreads();   // red[] may still be read from a previous use
   if (q) part_total<true>(p, q, V, R, red);
   else part_total<false>(p, q, V, R, red);
   __syncthreads();
   uint64_t W = 0;
-  for (int v = 0; v < kVerifyWaves; ++v) W += red[v];
+#pragma unroll
+  for (int v = 0; v < NW; ++v) W += red[v];
   return W;
 }
 
 // Smallest y with w(0) + ... + w(y) > t (t < the row's total weight), from the
 // part totals in red[]: the part that holds it, then running sums over that part.
+template <int NW>
 __device__ int row_find(const float* p, const float* q, int V, int R, uint64_t t, uint64_t* red,
                         int* found) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint64_t base = 0;
   int part = 0;
-  while (part < kVerifyWaves - 1 && base + red[part] <= t) base += red[part++];
+  while (part < NW - 1 && base + red[part] <= t) base += red[part++];
   const int64_t lo = static_cast<int64_t>(part) * R;
   const int64_t hi = min(static_cast<int64_t>(V), lo + R);
   if (tid == 0) *found = -1;
   const f32x4u zero = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t c0 = lo; c0 < hi; c0 += kFindPer * kVerifyThreads) {
+  for (int64_t c0 = lo; c0 < hi; c0 += kFindPer * 64 * NW) {
     const int64_t y0 = c0 + kFindPer * tid;
     uint64_t w[kFindPer / 4][4], own = 0;
 #pragma unroll
@@ -172,7 +175,7 @@ __device__ int row_find(const float* p, const float* q, int V, int R, uint64_t t
     __syncthreads();
     uint64_t before = base, total = 0;
 #pragma unroll
-    for (int v = 0; v < kVerifyWaves; ++v) {
+    for (int v = 0; v < NW; ++v) {
       if (v < wave) before += red[v];
       total += red[v];
     }
@@ -195,10 +198,11 @@ __device__ int row_find(const float* p, const float* q, int V, int R, uint64_t t
   return *found;
 }
 
-__global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void verify_kernel(VerifyArgs a) {
   const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int B = a.B, V = a.V;
-  __shared__ uint64_t red[kVerifyWaves];
+  __shared__ uint64_t red[NW];
   __shared__ int sh_m, sh_found;
   const int64_t prow0 = static_cast<int64_t>(s) * (B + 1);
   const int64_t qrow0 = static_cast<int64_t>(s) * B;
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
   __syncthreads();
   const int m = sh_m;
   int32_t* bits = a.accept_bits + qrow0;
-  for (int j = tid; j < B; j += kVerifyThreads) bits[j] = j < m ? 1 : 0;
+  for (int j = tid; j < B; j += 64 * NW) bits[j] = j < m ? 1 : 0;
   if (m < 0) {
     if (tid == 0) {
       a.accept_len[s] = 0;
@@ -239,17 +243,17 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
   }
   const float* p = a.p + (prow0 + m) * V;
   const float* q = m < B ? a.q + (qrow0 + m) * V : nullptr;
-  const int R = wave_tokens(V);
-  uint64_t W = row_total(p, q, V, R, red);
+  const int R = wave_tokens<NW>(V);
+  uint64_t W = row_total<NW>(p, q, V, R, red);
   if (W == 0 && q) {
     q = nullptr;
-    W = row_total(p, q, V, R, red);
+    W = row_total<NW>(p, q, V, R, red);
   }
   int next = -1;
   if (W) {
     const uint64_t u = a.words[prow0 + B];
     const uint64_t t = u * (W >> 32) + ((u * (W & 0xFFFFFFFFull)) >> 32);   // floor(u W / 2^32)
-    next = row_find(p, q, V, R, t, red, &sh_found);
+    next = row_find<NW>(p, q, V, R, t, red, &sh_found);
   }
   if (tid == 0) {
     a.accept_len[s] = m;
@@ -261,7 +265,20 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_kernel(VerifyArgs a) {
 
 hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
   if (a.S == 0) return hipSuccess;
-  hipLaunchKernelGGL(verify_kernel, dim3(a.S), dim3(kVerifyThreads), 0, stream, a);
+  // Wavefronts of a sequence's workgroup.  A long row wants sixteen, a short one is
+  // done by eight; many sequences fill the chip by themselves, and what counts is
+  // how many workgroups it holds at once (each a chain of barriers and two passes).
+  // us with 2, 4, 8, 16 wavefronts: 32 x 128000 tokens 107, 45, 25, 20; 256 x 2000
+  // 8, 8, 8, 11; 1024 x 1000 8, 8, 11, 23; 1024 x 32000 52, 43, 39, 49; 4096 x 1000
+  // 14, 22, 41, 94; 4096 x 32000 193, 159, 150, 199.  (Four wavefronts also keep
+  // S * threads within a launch's limit where sixteen would not.)
+  int nw = a.S <= 512 ? 8 : (a.S <= 1024 ? 4 : 2);
+  if (a.V > 16384 && nw < 8) nw *= 2;
+  if (a.V > 49152 && a.S <= 512) nw = 16;
+  if (nw == 16) hipLaunchKernelGGL(verify_kernel<16>, dim3(a.S), dim3(1024), 0, stream, a);
+  else if (nw == 8) hipLaunchKernelGGL(verify_kernel<8>, dim3(a.S), dim3(512), 0, stream, a);
+  else if (nw == 4) hipLaunchKernelGGL(verify_kernel<4>, dim3(a.S), dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(verify_kernel<2>, dim3(a.S), dim3(128), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -139,3 +139,16 @@ def test_verify_parts_of_a_row(V):
     words[1, 3] = 0xFFFFFFFF                              # the draw's largest and smallest words
     words[2, 3] = 0
     _check(w, draft, p, q, words, f"parts V={V}")
+
+
+@pytest.mark.parametrize("S,V", [(512, 300), (513, 300), (1024, 2049), (1025, 300), (1025, 16384), (1025, 16385),
+                                 (513, 16385), (512, 49152), (512, 49153), (3, 49153)])
+def test_verify_workgroup_sizes(S, V):
+    """Both sides of every line between the workgroup sizes (2, 4, 8 and 16 wavefronts,
+    by sequences and vocabulary): a few windows repeated, each with words of its own."""
+    _gpu()
+    w = wl.RAGGED32.replace(B=1, seed=0x5EED26)
+    draft, p, q, _ = wl.verify_inputs(w, 0, V, S=3)
+    at = np.arange(S) % 3
+    words = np.random.default_rng(S + V).integers(0, 2 ** 32, (S, 2), dtype=np.uint32)
+    _check(w, draft[at], p[at], q[at], words, f"sizes V={V}")
