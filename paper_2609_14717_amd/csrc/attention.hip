@@ -2229,16 +2229,21 @@ constexpr int kWavePartSeqs = 64;   // sequences (one per lane) up to which segm
 constexpr int stream_waves(int nqt) { return nqt; }
 constexpr int wg_streams(int hd, int nqt) { return nqt == 2 ? 1 : (hd == 128 ? 4 : 8); }
 
-// Tiles per part below which fewer are cut.  A walk of a few tiles is a chain of
-// latencies, so parts that a workgroup's streams merge in LDS are single tiles
-// (32 segments of 80-135 keys, 32 rows of 128: 21 us, 30 with parts of four; with
-// the extras 22, 35 with the own rows behind parts of four); parts of which each
-// leaves a record are of four (8 segments of 8-16K keys, 64 rows of 128: 47 us, 50
-// with parts of three), or of three where no segment of the launch has more than
-// two of those (33 rows of 64, 32 segments of 80-135 keys: 17 us, 19 with parts of
-// four and 17 with two, which take 19 instead of 16 at 20-60 keys).
-constexpr int wave_min_tiles(int hd, int nqt) { return nqt == 1 && hd == 128 ? 1 : 4; }
-constexpr int kShortParts = 3;
+// Tiles per part below which fewer are cut, by the most tiles of a segment.  A walk
+// of a few tiles is a chain of latencies, so parts that a workgroup's streams merge
+// in LDS (128 dims, up to 32 rows) are single tiles: 32 segments of 80-135 keys with
+// 32 rows 21 us, 30 with parts of four; with the extras 22, 35 with the own rows
+// behind parts of four.  From 384 tiles on they are two, as the records to combine
+// count (one segment of 16K keys 24 us with one, 23 with two and 24 with four, of
+// 32K 30, 26 and 26).  Parts of which each leaves a record are of four (8 segments of
+// 8-16K keys, 64 rows of 128: 47 us, 50 with three), or of three where no segment
+// has more than two of those (33 rows of 64, 32 segments of 80-135 keys: 17 us, 19
+// with four and 17 with two, which take 19 instead of 16 at 20-60 keys); with the
+// block's own rows a tile, parts of three would split it off alone.
+__device__ __forceinline__ int wave_min_tiles(int hd, int nqt, bool own, int most) {
+  if (nqt == 1) return hd == 128 ? (most < 384 ? 1 : 2) : 4;
+  return most <= 6 && !own ? 3 : 4;
+}
 constexpr int kSliceTiles = 4;   // tiles per slice of the even split below which fewer are cut
 
 // Header of the workspace (ints): tiles before each sequence [S+1], parts
@@ -2306,9 +2311,7 @@ __attribute__((amdgpu_num_vgpr(256))) void attn_wave_kernel(
     int mx = n_l;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) mx = max(mx, __shfl_xor(mx, off));
-    // (with the block's own rows a tile, parts of three would split it off alone)
-    const int t_min = NST == 1 && mx <= 2 * kShortParts && !(EXT && a.k_self)
-                          ? kShortParts : wave_min_tiles(HD, NQT);
+    const int t_min = wave_min_tiles(HD, NQT, EXT && a.k_self, mx);
     // lane c tries t = lo + c * step; ceil by a reciprocal (any count of at
     // least one part is a valid cut; every wavefront gets the same)
     auto cut = [&](int n, int t) {
