@@ -1,6 +1,7 @@
 """GPU parity of the full-precision round at the edges of its kernels: row tiles
 of 32, K split over sixteen wavefronts (fewer steps than wavefronts included),
-one and two query tiles, segments of one chunk (256 keys, finished in place) and
+E staged and read where it is used, windows within and past one ballot, one and two
+query tiles, segments of one chunk (256 keys, finished in place) and
 of several (records and the merge)."""
 import pytest
 
@@ -22,6 +23,11 @@ CASES = [
     (7, 5, 256, 320, 6, 2, 128, 5, 520),       # 21 query rows at head_dim 128
     (16, 2, 256, 128, 8, 2, 128, 15, 700),     # 64 query rows at head_dim 128
     (31, 1, 128, 64, 2, 1, 64, 17000, 17000),  # more than 64 chunks of 256 keys
+    (5, 7, 4160, 64, 2, 1, 64, 10, 60),        # more E than is staged in LDS
+    (16, 2, 4096, 64, 2, 1, 64, 10, 60),       # as much as is
+    (33, 3, 256, 128, 1, 1, 64, 20, 300),      # windows one ballot of a row tile reaches back over,
+    (34, 3, 256, 128, 1, 1, 64, 20, 300),      # and longer ones: every row reads its own tokens
+    (64, 2, 4160, 64, 1, 1, 128, 20, 300),     # both
 ]
 
 
