@@ -39,7 +39,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kMaxChunkPages = 256;   // page-id staging capacity (fp32 chunk / bf16 sub-chunk)
+constexpr int kMaxChunkPages = 256;   // pages of the longest fp32 chunk (wider page tables are refused)
 
 struct SeqInfo {
   int ctx, carry, npc, npt, nch;
@@ -1577,8 +1577,8 @@ __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(AttnArgs a, int 
 
 // ------------------------------------------------ bf16 32-key tile arithmetic
 //
-// Used by the grouped-prefix kernel below.  One wavefront
-// owns NQT query tiles of 32 rows; the products use v_mfma_f32_32x32x16_bf16
+// Of the streams and of the grouped-prefix kernel.  One wavefront owns NQT query
+// tiles of 32 rows; the products use v_mfma_f32_32x32x16_bf16
 // on 32 keys x 32 query rows.  S^T = K . Q^T takes K row rho from key pi(rho),
 // pi swapping bits 2 and 3 of the key index; then lane l holds, for query
 // l % 32, the keys 8*(l/32) .. +7 of both pages of the tile (registers 0-7:
