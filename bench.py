@@ -27,6 +27,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -206,10 +207,10 @@ def summarize_pmc(args):
     def one(table, counter, name, window=None):
         """Sum over the kernels matching ``name`` of the mean per dispatch (over
         the window of dispatches if given), and the dispatches averaged."""
-        # the plain instantiations only: the EXT ones (last template argument
-        # true) serve drafter_block_attention_ext, timed separately
+        # the plain instantiations only: the EXT ones serve
+        # drafter_block_attention_ext, timed separately
         rows = [v for k, v in table.items()
-                if k[1] == counter and name in k[0] and "true>" not in k[0]]
+                if k[1] == counter and name in k[0] and not is_ext(k[0])]
         if not rows:
             raise SystemExit(f"no {counter} rows for {name}")
         tot, cnt = 0.0, 0
@@ -366,6 +367,12 @@ def is_kernel(name, kernel):
     return "::" + kernel + "<" in name or "::" + kernel + "(" in name
 
 
+def is_ext(name):
+    """An attention kernel's EXT instantiation: its first bool template argument."""
+    bools = re.findall(r"\b(true|false)\b", name)
+    return bools[:1] == ["true"]
+
+
 def summarize_stats(args):
     rows = []
     with open(args.summarize_stats) as fh:
@@ -381,9 +388,8 @@ def summarize_stats(args):
     for n, c, a, lo, hi, pct in rows:
         short = n if len(n) <= 90 else n[:87] + "..."
         lines.append(f"{short:90s} {c:6d} {a:8.2f} {lo:8.2f} {hi:8.2f} {pct:6.2f}")
-    # the plain instantiations (the EXT ones, last template argument true, serve
-    # drafter_block_attention_ext)
-    att = [(k, r) for k in ATTN_KERNELS for r in rows if is_kernel(r[0], k) and "true>" not in r[0]]
+    # the plain instantiations (the EXT ones serve drafter_block_attention_ext)
+    att = [(k, r) for k in ATTN_KERNELS for r in rows if is_kernel(r[0], k) and not is_ext(r[0])]
     if att:
         lines += ["", "drafter_block_attention, all dispatches = " + " + ".join(
             f"{k} {r[2]:.2f} us" for k, r in att) +
@@ -397,7 +403,7 @@ def summarize_stats(args):
         with open(trace) as fh:
             for r in csv.DictReader(fh):
                 for k, _ in att:
-                    if is_kernel(r["Kernel_Name"], k) and "true>" not in r["Kernel_Name"]:
+                    if is_kernel(r["Kernel_Name"], k) and not is_ext(r["Kernel_Name"]):
                         per.setdefault(k, []).append(
                             (int(r["Dispatch_Id"]),
                              (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
