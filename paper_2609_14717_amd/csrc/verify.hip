@@ -13,7 +13,7 @@
 //     a correction whose weights are all zero): y is the smallest token whose
 //     running integer sum exceeds floor(word * W / 2^32), W the total weight.
 //
-// One workgroup of 2 to 16 wavefronts per sequence, by their number and the row's
+// One workgroup of 1 to 16 wavefronts per sequence, by their number and the row's
 // length (no scratch memory reaches this call, so a row's total is not summed
 // across workgroups).  The first wavefront takes the acceptance decisions with one
 // ballot per 64 positions.  Then the row of p (and q) is read once: every wavefront
@@ -271,14 +271,18 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
   // us with 2, 4, 8, 16 wavefronts: 32 x 128000 tokens 107, 45, 25, 20; 256 x 2000
   // 8, 8, 8, 11; 1024 x 1000 8, 8, 11, 23; 1024 x 32000 52, 43, 39, 49; 4096 x 1000
   // 14, 22, 41, 94; 4096 x 32000 193, 159, 150, 199.  (Four wavefronts also keep
-  // S * threads within a launch's limit where sixteen would not.)
+  // S * threads within a launch's limit where sixteen would not.)  Short rows of still
+  // more sequences take one: with 1 and 2 wavefronts 4096 x 16 8.5, 11.7; 4096 x 1000
+  // 11, 15; 30000 x 100 43, 77; but 2048 x 1000 8.6, 8.4 and 8192 x 2000 41, 40.
   int nw = a.S <= 512 ? 8 : (a.S <= 1024 ? 4 : 2);
   if (a.V > 16384 && nw < 8) nw *= 2;
   if (a.V > 49152 && a.S <= 512) nw = 16;
+  if (a.V <= 1024 && a.S > 2048) nw = 1;
   if (nw == 16) hipLaunchKernelGGL(verify_kernel<16>, dim3(a.S), dim3(1024), 0, stream, a);
   else if (nw == 8) hipLaunchKernelGGL(verify_kernel<8>, dim3(a.S), dim3(512), 0, stream, a);
   else if (nw == 4) hipLaunchKernelGGL(verify_kernel<4>, dim3(a.S), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(verify_kernel<2>, dim3(a.S), dim3(128), 0, stream, a);
+  else if (nw == 2) hipLaunchKernelGGL(verify_kernel<2>, dim3(a.S), dim3(128), 0, stream, a);
+  else hipLaunchKernelGGL(verify_kernel<1>, dim3(a.S), dim3(64), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -142,9 +142,10 @@ def test_verify_parts_of_a_row(V):
 
 
 @pytest.mark.parametrize("S,V", [(512, 300), (513, 300), (1024, 2049), (1025, 300), (1025, 16384), (1025, 16385),
-                                 (513, 16385), (512, 49152), (512, 49153), (3, 49153)])
+                                 (513, 16385), (512, 49152), (512, 49153), (3, 49153), (2048, 1024), (2049, 1024),
+                                 (2049, 1025), (2049, 3)])
 def test_verify_workgroup_sizes(S, V):
-    """Both sides of every line between the workgroup sizes (2, 4, 8 and 16 wavefronts,
+    """Both sides of every line between the workgroup sizes (1, 2, 4, 8 and 16 wavefronts,
     by sequences and vocabulary): a few windows repeated, each with words of its own."""
     _gpu()
     w = wl.RAGGED32.replace(B=1, seed=0x5EED26)
